@@ -187,6 +187,43 @@ __device__ __forceinline__ void wave_bitonic_sort(uint64_t (&v)[E])
     }
 }
 
+__device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src)
+{
+    const uint32_t lo = __shfl((uint32_t)v, src, 64);
+    const uint32_t hi = __shfl((uint32_t)(v >> 32), src, 64);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// Ascending bitonic merge of a bitonic sequence of 64*E keys held E per lane
+// (element i = e*64 + lane).
+template <int E>
+__device__ __forceinline__ void wave_bitonic_merge(uint64_t (&v)[E])
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int j = 32 * E; j > 0; j >>= 1) {
+        if (j >= 64) {
+            const int je = j >> 6;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int pe = e ^ je;
+                if (pe > e) {
+                    const uint64_t a = v[e], b = v[pe];
+                    v[e] = a < b ? a : b;
+                    v[pe] = a < b ? b : a;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const uint64_t o = shfl_xor_u64(v[e], j);
+                const bool lower = (lane & j) == 0;
+                v[e] = lower ? (o < v[e] ? o : v[e]) : (o < v[e] ? v[e] : o);
+            }
+        }
+    }
+}
+
 template <int E>
 __device__ __forceinline__ int wave_sort_compact_e(uint64_t *buf, int n, int k)
 {

@@ -112,26 +112,88 @@ __global__ __launch_bounds__(1024) void k_list_order(const int64_t *offsets, int
 }
 
 // ---- merge of per-part top-k keys -----------------------------------------
-// One wavefront per query selects the k smallest of n_parts * k keys.
-__global__ __launch_bounds__(64) void k_topk_merge(const uint64_t *keys, int64_t nq, int n_parts, int k,
-                                                   int metric, int32_t *ids, float *dist)
+// One workgroup of W waves per query folds the parts' sorted key lists (k
+// keys each, kNoKey past the valid ones) into the KS = 64 E >= k smallest,
+// kept sorted in registers.  A wave takes every W-th piece: with k <= 64 a
+// piece is 64 consecutive keys, whatever lists they belong to, sorted first;
+// with more it is one list.  A piece with no key below the wave's k-th best
+// is passed over, which after the first few pieces is nearly all of them.
+// The waves' lists then meet in LDS, halving the waves each time.  The
+// selection this replaces scanned all keys once per result (178 us for 4,096
+// queries of 8 parts x 100 keys, 43 us for one query of 246 parts x 10
+// keys); this form takes 16 us and 10 us.
+template <int E>
+__global__ __launch_bounds__(1024) void k_topk_merge(const uint64_t *keys, int n_parts, int k, int metric,
+                                                     int32_t *ids, float *dist)
 {
-    extern __shared__ uint64_t mk[];
-    const int64_t i = blockIdx.x;
-    const int lane = threadIdx.x;
-    const int n = n_parts * k;
-    for (int t = lane; t < n; t += 64) mk[t] = keys[i * n + t];
-    uint64_t *out = mk + n;
-    int got = wave_select_smallest(mk, n, k, out);
-    for (int r = lane; r < k; r += 64) {
-        int32_t sid = -1;
-        float sv = metric == LVQ_L2 ? __uint_as_float(0x7F800000u) : __uint_as_float(0xFF800000u);
-        if (r < got) {
-            sid = (int32_t)(uint32_t)out[r];
-            sv = key_score(out[r], metric);
+    extern __shared__ __align__(16) unsigned char smem[];
+    uint64_t *lists = reinterpret_cast<uint64_t *>(smem);   // W x KS, W > 1
+    const int64_t qi = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
+    const int64_t n = (int64_t)n_parts * k;
+    const uint64_t *src = keys + qi * n;
+    const int piece = E == 1 ? 64 : k;                       // keys per piece
+    const int n_pieces = E == 1 ? (int)((n + 63) / 64) : n_parts;
+    uint64_t top[E], nx[E];
+    auto load = [&](int p) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int i = e * 64 + lane;
+            const int64_t at = (int64_t)p * piece + i;
+            nx[e] = p < n_pieces && i < piece && at < n ? src[at] : kNoKey;
         }
-        ids[i * k + r] = sid;
-        dist[i * k + r] = sv;
+    };
+    auto fold = [&](const uint64_t (&v)[E]) {                // v sorted
+        uint64_t r[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) r[e] = shfl_u64(v[E - 1 - e], 63 - lane);
+#pragma unroll
+        for (int e = 0; e < E; ++e) top[e] = min_u64(top[e], r[e]);
+        wave_bitonic_merge<E>(top);
+    };
+    auto kth = [&]() {
+        uint64_t b = kNoKey;
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (e == ((k - 1) >> 6)) b = top[e];
+        return readlane_u64(b, (k - 1) & 63);
+    };
+#pragma unroll
+    for (int e = 0; e < E; ++e) top[e] = kNoKey;
+    uint64_t bound = kNoKey;
+    load(wave);
+    for (int p = wave; p < n_pieces; p += W) {
+        uint64_t v[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = nx[e];
+        load(p + W);
+        // (E > 1: a list's smallest key is its first)
+        if (!__ballot(v[0] < bound)) continue;
+        if constexpr (E == 1) wave_bitonic_sort<1>(v);
+        fold(v);
+        bound = kth();
+    }
+    for (int h = W >> 1; h > 0; h >>= 1) {
+        if (wave >= h && wave < 2 * h)
+#pragma unroll
+            for (int e = 0; e < E; ++e) lists[(size_t)wave * 64 * E + e * 64 + lane] = top[e];
+        __syncthreads();
+        if (wave < h) {
+            uint64_t v[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) v[e] = lists[(size_t)(wave + h) * 64 * E + e * 64 + lane];
+            fold(v);
+        }
+    }
+    if (wave != 0) return;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = e * 64 + lane;
+        if (i >= k) continue;
+        const bool got = top[e] != kNoKey;
+        ids[qi * k + i] = got ? (int32_t)(uint32_t)top[e] : -1;
+        dist[qi * k + i] = got ? key_score(top[e], metric)
+                               : __uint_as_float(metric == LVQ_L2 ? 0x7F800000u : 0xFF800000u);
     }
 }
 
@@ -505,9 +567,19 @@ hipError_t launch_topk_merge(const uint64_t *keys, int64_t nq, int n_parts, int 
                              float *dist, hipStream_t s)
 {
     if (nq <= 0) return hipSuccess;
-    size_t lds = ((size_t)n_parts * k + k) * sizeof(uint64_t);
-    hipLaunchKernelGGL(k_topk_merge, dim3((unsigned)nq), dim3(64), lds, s, keys, nq, n_parts, k, metric, ids,
-                       dist);
+    if (k < 1 || k > kMaxTopK || n_parts < 1) return hipErrorInvalidValue;
+    int E = 1;
+    while (64 * E < k) E *= 2;
+    // waves per query: while each has two pieces to fold and the batch leaves
+    // wave slots idle (a full chip holds 8,192 waves; the halving steps cost
+    // about two pieces each), within 64 KB of LDS
+    const int64_t pieces = E == 1 ? ((int64_t)n_parts * k + 63) / 64 : n_parts;
+    int W = 1;
+    while (W < 16 && 4 * W <= pieces && nq * W < 2048 && (size_t)2 * W * 64 * E * sizeof(uint64_t) <= 65536) W *= 2;
+    const size_t lds = W > 1 ? (size_t)W * 64 * E * sizeof(uint64_t) : 0;
+    auto kern = E == 1 ? k_topk_merge<1> : E == 2 ? k_topk_merge<2> : E == 4 ? k_topk_merge<4>
+              : E == 8 ? k_topk_merge<8> : k_topk_merge<16>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)nq), dim3(64 * W), lds, s, keys, n_parts, k, metric, ids, dist);
     return hipGetLastError();
 }
 
