@@ -50,30 +50,6 @@ size_t wide_lds(int qb, int kpos, int rb, int prec, int bits2, int n_means)
     return wide_lds_bytes(qb, kpos, rb, prec == LVQ_FP32 ? 4 : 2, mm ? n_means : 0, 12 + (mm ? 4 : 0) + (ch2 ? 4 : 0));
 }
 
-// FP32 query fragments from kernel-order queries (nq x kpos, zero at padding
-// positions): [tile][block][chunk][step][lane] float4s, element e of step s
-// being the value for MFMA 4 s + e, whose lane l holds position
-// CHUNK_POS c + (CHUNK_POS / 2)(l >> 5) + 4 s + e of query 32 block + (l & 31)
-// (zero past nq) -- the positions of the codes that code_words hands that lane.
-__global__ __launch_bounds__(256) void k_frag32(const float *qk, int64_t nq, int kpos, int chunk_pos, int qb,
-                                                float4 *frag)
-{
-    const int nchunk = kpos / chunk_pos, steps = chunk_pos / 8;
-    const int64_t per_tile = (int64_t)qb * nchunk * steps * 64;
-    const int64_t tile = blockIdx.x;
-    for (int64_t e = threadIdx.x; e < per_tile; e += 256) {
-        const int l = (int)(e % 64);
-        const int s = (int)((e / 64) % steps);
-        const int c = (int)((e / (64 * steps)) % nchunk);
-        const int b = (int)(e / (64 * steps * nchunk));
-        const int64_t gq = tile * 32 * qb + 32 * b + (l & 31);
-        const int p = c * chunk_pos + (l >> 5) * (chunk_pos / 2) + 4 * s;
-        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (gq < nq) v = *reinterpret_cast<const float4 *>(qk + gq * kpos + p);
-        frag[tile * per_tile + e] = v;
-    }
-}
-
 }  // namespace
 
 int mfma_wide_query_block(int bits1, int bits2, int kpos, int prec, int k, int n_means, size_t lds_max)
@@ -108,17 +84,6 @@ hipError_t launch_scan_mfma_wide(const ScanArgs &a, int bits1, int bits2, int pr
     const size_t lds = wide_lds(qb, a.kpos, rb, prec, bits2, a.n_means);
     if (lds > lds_max) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * wide_waves(rb)), lds, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_frag32(const float *qk, int64_t nq, int kpos, int bits1, int qb, void *frag, hipStream_t s)
-{
-    const int chunk_pos = bits1 == 8 ? 32 : 64;
-    if (qb < 1 || (bits1 != 4 && bits1 != 8) || kpos % chunk_pos) return hipErrorInvalidValue;
-    if (nq <= 0) return hipSuccess;
-    const int64_t tiles = (nq + 32 * qb - 1) / (32 * qb);
-    hipLaunchKernelGGL(k_frag32, dim3((unsigned)tiles), dim3(256), 0, s, qk, nq, kpos, chunk_pos, qb,
-                       reinterpret_cast<float4 *>(frag));
     return hipGetLastError();
 }
 

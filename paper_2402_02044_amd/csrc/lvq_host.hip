@@ -1050,27 +1050,19 @@ static int topk_mfma(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq,
     Workspace &w = workspace(ix, s);
     const int tq = 32 * qb;
     const int64_t qtiles = (nq + tq - 1) / tq;
-    if (prec == LVQ_FP32) {
-        // kernel-order FP32 queries, sum(q) and c_m, then their MFMA fragments
-        if ((rc = prep_queries(ix, w, (const float *)q_dev, nq, s))) return rc;
-        if ((rc = dev_alloc(ix, w.q16, (size_t)qtiles * tq * f.kpos * 4))) return rc;
-        LVQ_HIP(launch_frag32(P<float>(w.qk), nq, f.kpos, f.bits1, qb, w.q16.p, s));
-    } else {
-        if ((rc = dev_alloc(ix, w.q16, (size_t)qtiles * tq * f.kpos * 2))) return rc;
-        if ((rc = dev_alloc(ix, w.qsum, sizeof(float) * (size_t)nq))) return rc;
-        if ((rc = dev_alloc(ix, w.cm, sizeof(float) * (size_t)nq * ix->n_means))) return rc;
-        LVQ_HIP(launch_prep16(q_dev, nq, f.dim, f.kpos, f.bits1, qb, prec, P<int32_t>(ix->kdim), P<float>(ix->means),
-                              ix->n_means, w.q16.p, P<float>(w.qsum), P<float>(w.cm), s));
-    }
+    if ((rc = dev_alloc(ix, w.q16, (size_t)qtiles * tq * f.kpos * (prec == LVQ_FP32 ? 4 : 2)))) return rc;
+    if ((rc = dev_alloc(ix, w.qsum, sizeof(float) * (size_t)nq))) return rc;
+    if ((rc = dev_alloc(ix, w.cm, sizeof(float) * (size_t)nq * ix->n_means))) return rc;
+    if ((rc = dev_alloc(ix, w.gthr, sizeof(uint32_t) * (size_t)nq))) return rc;
+    LVQ_HIP(launch_prep_scan(q_dev, nq, f.dim, f.kpos, f.bits1, qb, prec, P<int32_t>(ix->kdim), P<float>(ix->means),
+                             ix->n_means, w.q16.p, P<float>(w.qsum), P<float>(w.cm), P<uint32_t>(w.gthr), s));
     const int64_t n_rows = ix->list_len;
     int64_t grid = 0;
     const int64_t parts =
         qbw ? scan_parts_wide(ix, qtiles, k, n_rows, prec, &grid) : scan_parts_mfma(ix, qtiles, k, n_rows);
     const int64_t rows_per_part = std::max<int64_t>(1, (n_rows + parts - 1) / parts);
     if ((rc = dev_alloc(ix, w.part, sizeof(uint64_t) * (size_t)nq * parts * k))) return rc;
-    if ((rc = dev_alloc(ix, w.gthr, sizeof(uint32_t) * (size_t)nq))) return rc;
     if (qbw && (rc = dev_alloc(ix, w.mkeys, sizeof(uint64_t) * (size_t)grid * tq * mfma_wide_cap(k)))) return rc;
-    LVQ_HIP(launch_fill_u32(P<uint32_t>(w.gthr), 0xFFFFFFFFu, nq, s));
     ScanArgs a;
     a.rows = P<uint8_t>(ix->rows);
     a.resid = P<uint8_t>(ix->resid);

@@ -270,8 +270,7 @@ typedef void (*MfmaKernelPtr)(ScanArgs);
 MfmaKernelPtr mfma_kernel_first(int bits1, int kpos, int fp16, int *qb);
 MfmaKernelPtr mfma_kernel_full(int bits1, int kpos, int fp16, int *qb);
 // MFMA exhaustive scan: 32-query blocks per workgroup for a format (0 when
-// the code width / position count has no instantiation), its LDS bytes, and
-// the query-fragment precompute for bf16 / fp16 queries.
+// the code width / position count has no instantiation) and its LDS bytes.
 int mfma_query_block(int bits1, int bits2, int kpos);
 size_t mfma_lds_bytes(int qb, int n_means, int k, int capq);
 int mfma_capq(int qb, int n_means, int k, size_t lds_max);
@@ -284,18 +283,18 @@ int mfma_capq(int qb, int n_means, int k, size_t lds_max);
 // power of two, at least 64) and the key-region capacity per query, and the
 // launch of a persistent grid (a multiple of 8 workgroups, each owning
 // 32*qb*cap keys of a.mkeys; a.mks and a.mcap as these functions give them).
-// The FP32 forms read a.q16 as the fragments launch_frag32 writes from
-// kernel-order queries (nq x kpos FP32, as prep_queries leaves them):
-// 32*qb*kpos*4 bytes per tile of 32*qb queries; and a.cm as nq x n_means.
+// launch_prep_scan prepares a scan of either matrix-core kernel: a.q16, the
+// queries as MFMA fragments (32*qb*kpos*2 bytes per tile of 32*qb queries, 4
+// bytes per value in FP32), a.qsum, a.cm (nq x n_means) and a.gthr, reset to
+// no bound.
 int mfma_wide_query_block(int bits1, int bits2, int kpos, int prec, int k, int n_means, size_t lds_max);
 int mfma_wide_sorted(int k);
 int mfma_wide_cap(int k);
 hipError_t launch_scan_mfma_wide(const ScanArgs &a, int bits1, int bits2, int prec, int64_t grid, size_t lds_max,
                                  hipStream_t s);
-hipError_t launch_frag32(const float *qk, int64_t nq, int kpos, int bits1, int qb, void *frag, hipStream_t s);
-hipError_t launch_prep16(const void *q, int64_t nq, int dim, int kpos, int bits1, int qb, int prec,
-                         const int32_t *kdim, const float *means, int n_means, void *frag, float *qsum, float *cm,
-                         hipStream_t s);
+hipError_t launch_prep_scan(const void *q, int64_t nq, int dim, int kpos, int bits1, int qb, int prec,
+                            const int32_t *kdim, const float *means, int n_means, void *frag, float *qsum, float *cm,
+                            uint32_t *gthr, hipStream_t s);
 // fp32 -> bf16 / fp16 (LVQ_BF16 / LVQ_FP16), round to nearest even, n values.
 hipError_t launch_cast16(const float *x, int64_t n, int prec, void *out, hipStream_t s);
 hipError_t launch_topk_merge(const uint64_t *part_keys, int64_t nq, int n_parts, int k, int metric,
