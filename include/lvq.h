@@ -208,7 +208,8 @@ int lvq_set_tile(lvq_index *index, int32_t level, int32_t topk, int32_t shape);
  * parameters of one: lanes per candidate, bytes per load, loads per lane and
  * round, pipeline flags (bit 0 software-pipelined, bit 1 query in
  * registers, bit 2 two blocks ahead, bit 3 registers allotted for at least
- * six waves per SIMD).  Outputs may be NULL.                              */
+ * six waves per SIMD, bits 4 and 5 values summed in the order of 16 lanes per
+ * candidate).  Outputs may be NULL.                                       */
 int lvq_num_tile_shapes(void);
 int lvq_tile_shape(int32_t shape, int32_t *lanes, int32_t *piece_bytes, int32_t *pieces, int32_t *pipe);
 

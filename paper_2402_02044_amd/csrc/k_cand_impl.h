@@ -284,26 +284,71 @@ struct QRegs {
     float4 v[NCH][CandGeom<B1, CH>::kF4];
 };
 
+// Order of a similarity's sum.  A lane adds its own pieces up in order and a
+// group of lanes adds its sums up as a binary tree, so the order, and with it
+// the last bit of every value, depends on how many lanes share a row.  The
+// layouts below keep the order of the 16-lane shapes while giving a lane
+// more of the row, so that they can stand in for those by default:
+//   kOrdLane    the shape's own order: one sum per lane
+//   kOrdQuads   the order of 16 lanes with one piece each (rows of at most 16
+//               pieces) on 4 lanes: lane g holds pieces 4c + g, c < NCH, each
+//               with a sum of its own, and the tree's upper levels join the
+//               four-lane sums of c = 0, 1 and 2, 3
+//   kOrdHalves  the order of twice the lanes with pieces half as long: a
+//               16-byte piece has two sums, one per half, joined first
+constexpr int kOrdLane = 0, kOrdQuads = 1, kOrdHalves = 2;
+template <int NCH, int ORD>
+constexpr int kSums = ORD == kOrdQuads ? NCH : ORD == kOrdHalves ? 2 : 1;
+
+// The tree over a candidate's sums; every lane of the group gets the total.
+template <int G, int NCH, int ORD>
+__device__ __forceinline__ float tree_sum(const float (&x)[kSums<NCH, ORD>])
+{
+    if constexpr (ORD == kOrdQuads) {
+        static_assert(G == 4 && NCH <= 4, "four-lane sums");
+        float q[4];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) q[c] = group_sum<G>(x[c]);
+        if constexpr (NCH == 1) return q[0];
+        else if constexpr (NCH == 2) return q[0] + q[1];
+        else if constexpr (NCH == 3) return (q[0] + q[1]) + q[2];
+        else return (q[0] + q[1]) + (q[2] + q[3]);
+    } else if constexpr (ORD == kOrdHalves) {
+        return group_sum<G>(x[0] + x[1]);
+    } else {
+        return group_sum<G>(x[0]);
+    }
+}
+
 // Accumulate the loaded pieces of one candidate; query values come from the
 // LDS table tq or, when QREG is set, from registers.  Pieces past the end
 // (u >= npieces) hold zero codes; their L2 contribution is dropped by a
 // select, their IP contribution is zero already.
-template <int B1, int B2, int METRIC, bool MASK, int G, int CH, int NCH, bool QREG>
+template <int B1, int B2, int METRIC, bool MASK, int G, int CH, int NCH, bool QREG, int ORD>
 __device__ __forceinline__ void accumulate_pair(const PairRegs<B1, B2, CH, NCH> &P, const float *tq,
-                                                const QRegs<B1, CH, NCH> &qr, const float *mtab, int p0,
-                                                int g, int npieces, const L2Row &R, Acc &A, float &l2acc)
+                                                const QRegs<B1, CH, NCH> &qr, const float *mtab,
+                                                const float4 *zero, int p0, int g, int npieces, const L2Row &R,
+                                                Acc (&A)[kSums<NCH, ORD>],
+                                                float (&l2acc)[kSums<NCH, ORD>])
 {
+    static_assert(ORD != kOrdHalves || CH == 16, "two halves of 8 bytes");
     using Geo = CandGeom<B1, CH>;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         const int u = p0 + c * G + g;
         const bool ok = u < npieces;
         const int uu = ok ? u : 0;
+        // kept orders, inner product: a lane with no piece reads zeros (the
+        // 16-lane shapes read piece 0 there; CandArgs::idle_slots says when)
+        constexpr bool ZERO = ORD != kOrdLane && METRIC == LVQ_IP && !QREG;
+        const float4 *q4 = reinterpret_cast<const float4 *>(tq) + uu;
+        const int step = ZERO && !ok ? 0 : npieces;
+        if (ZERO && !ok) q4 = zero;
         float qv[Geo::kSlots];
         float mv[MASK ? Geo::kSlots : 1];
 #pragma unroll
         for (int r = 0; r < Geo::kF4; ++r) {
-            float4 f = QREG ? qr.v[c][r] : reinterpret_cast<const float4 *>(tq)[r * npieces + uu];
+            float4 f = QREG ? qr.v[c][r] : q4[r * step];
             qv[4 * r] = f.x; qv[4 * r + 1] = f.y; qv[4 * r + 2] = f.z; qv[4 * r + 3] = f.w;
             if constexpr (MASK) {
                 float4 mm = reinterpret_cast<const float4 *>(mtab)[r * npieces + uu];
@@ -311,16 +356,23 @@ __device__ __forceinline__ void accumulate_pair(const PairRegs<B1, B2, CH, NCH> 
             }
         }
         constexpr int kQW = B1 == 4 ? 8 : 4;   // query values per word
-        float part = 0.0f;
+        constexpr int PARTS = ORD == kOrdHalves ? 2 : 1;   // sums of one piece
+        float part[PARTS];
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) part[i] = 0.0f;
 #pragma unroll
         for (int wi = 0; wi < Geo::kWords; ++wi) {
+            const int h = wi * PARTS / Geo::kWords;
             if constexpr (METRIC == LVQ_IP)
-                ip_word<B1, B2>(P.wv[c].w[wi], qv + kQW * wi, P.rv[c].w, wi, A);
+                ip_word<B1, B2>(P.wv[c].w[wi], qv + kQW * wi, P.rv[c].w, wi, A[ORD == kOrdQuads ? c : h]);
             else
                 l2_word<B1, B2, MASK>(P.wv[c].w[wi], qv + kQW * wi, MASK ? mv + kQW * wi : nullptr,
-                                      P.rv[c].w, wi, R, part);
+                                      P.rv[c].w, wi, R, part[h]);
         }
-        if constexpr (METRIC == LVQ_L2) l2acc += ok ? part : 0.0f;
+        if constexpr (METRIC == LVQ_L2) {
+#pragma unroll
+            for (int h = 0; h < PARTS; ++h) l2acc[ORD == kOrdQuads ? c : h] += ok ? part[h] : 0.0f;
+        }
     }
 }
 
@@ -338,26 +390,31 @@ __device__ __forceinline__ L2Row l2_row(float4 hdr)
 
 // Final value of one candidate from its group's accumulators (all lanes of
 // the group return the same value).
-template <int B2, int METRIC, int G>
-__device__ __forceinline__ float finish_pair(const Acc &A, float l2acc, float4 hdr, const float *cmt, int n_means,
-                                             float qsum)
+template <int B2, int METRIC, int G, int NCH, int ORD>
+__device__ __forceinline__ float finish_pair(const Acc (&A)[kSums<NCH, ORD>], const float (&l2acc)[kSums<NCH, ORD>],
+                                             float4 hdr, const float *cmt, int n_means, float qsum)
 {
     if constexpr (METRIC == LVQ_IP) {
-        float a1 = fmaf(A.a_hi, 0.0625f, A.a_lo);
-        a1 = group_sum<G>(a1);
+        constexpr int N = kSums<NCH, ORD>;
+        float s1[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) s1[i] = fmaf(A[i].a_hi, 0.0625f, A[i].a_lo);
+        const float a1 = tree_sum<G, NCH, ORD>(s1);
         const float l = hdr.x, dl = hdr.y, dl2 = hdr.z;
         const int mid = (int)(__float_as_uint(hdr.w) & 0xFFu);
         const float lp = B2 ? l - 0.5f * dl : l;
         float score = fmaf(lp, qsum, cmt[mid < n_means ? mid : 0]);
         score = fmaf(dl, a1, score);
         if constexpr (B2 != 0) {
-            float a2 = fmaf(A.r_hi, 0.0625f, A.r_lo);
-            a2 = group_sum<G>(a2);
+            float s2[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) s2[i] = fmaf(A[i].r_hi, 0.0625f, A[i].r_lo);
+            const float a2 = tree_sum<G, NCH, ORD>(s2);
             score = fmaf(dl2, a2, score);
         }
         return score;
     } else {
-        return group_sum<G>(l2acc);
+        return tree_sum<G, NCH, ORD>(l2acc);
     }
 }
 
@@ -391,11 +448,13 @@ __device__ __forceinline__ int table_of(uint32_t mid, bool sub, const uint8_t *t
 // or two blocks ahead are in flight while the current block is consumed.
 // WAVES: the fewest waves per SIMD the register allocation must allow (1: no
 // constraint); small tiles trade a few registers for more rows in flight.
-template <int B1, int B2, int METRIC, bool MULTI, bool MASK, int G, int CH, int NCH, int PIPE, bool QREG, int WAVES>
+template <int B1, int B2, int METRIC, bool MULTI, bool MASK, int G, int CH, int NCH, int PIPE, bool QREG, int WAVES,
+          int ORD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8))) void k_cand(CandArgs a)
 {
     static_assert(!QREG || (PIPE && !MULTI && !MASK), "register-resident query needs one table, one round");
     static_assert(PIPE >= 0 && PIPE <= 2, "pipeline depth");
+    static_assert(ORD == kOrdLane || PIPE, "a row in one round");
     using Regs = PairRegs<B1, B2, CH, NCH>;
     constexpr int kPairsPerWave = 64 / G;
     constexpr int kPairsPerBlock = 4 * kPairsPerWave;
@@ -435,6 +494,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
     uint64_t *keys = reinterpret_cast<uint64_t *>(sbase + (seg ? nseg + 1 : 0));
     uint64_t *wbuf = keys + (size_t)wave * a.cw;
     uint64_t *merge = keys + (size_t)4 * a.cw;
+    __shared__ float4 s_zero;
+    if (tid == 0) s_zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // read after the lists' barriers
     __shared__ int s_item;
     __shared__ int s_got[4];
 
@@ -494,7 +555,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
             }
             __syncthreads();
         }
-        const float qsum = METRIC == LVQ_IP ? a.qsum[list] : 0.0f;
+        float qsum = METRIC == LVQ_IP ? a.qsum[list] : 0.0f;
+        // (see CandArgs::idle_slots: adds 0, or NaN)
+        if constexpr (METRIC == LVQ_IP)
+            for (int sp = 0; sp < a.idle_slots; ++sp) qsum = fmaf(qtab[qtab_index<B1, CH>(sp, npieces)], 0.0f, qsum);
         QRegs<B1, CH, NCH> qr;
         if constexpr (QREG) {
 #pragma unroll
@@ -535,8 +599,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
         }
         for (int64_t base = e0; base < e1; base += kPairsPerBlock) {
             const int64_t e = base + my;
-            Acc A{0.f, 0.f, 0.f, 0.f};
-            float l2acc = 0.0f;
+            Acc A[kSums<NCH, ORD>];
+            float l2acc[kSums<NCH, ORD>];
+#pragma unroll
+            for (int i = 0; i < kSums<NCH, ORD>; ++i) {
+                A[i] = Acc{0.f, 0.f, 0.f, 0.f};
+                l2acc[i] = 0.0f;
+            }
             float4 hdr;
             uint2 ep;
             bool valid, work;
@@ -552,7 +621,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
                                               ? (size_t)table_of(__float_as_uint(hdr.w) & 0xFFu, sub, tmap, ntab) * a.kpos
                                               : 0);
                 const L2Row R = l2_row<B2>(hdr);
-                accumulate_pair<B1, B2, METRIC, MASK, G, CH, NCH, QREG>(cur, tq, qr, mtab, 0, g, npieces, R, A,
+                accumulate_pair<B1, B2, METRIC, MASK, G, CH, NCH, QREG, ORD>(cur, tq, qr, mtab, &s_zero, 0, g, npieces, R, A,
                                                                         l2acc);
                 valid = cur.valid;
                 work = cur.work;
@@ -575,16 +644,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
                                               ? (size_t)table_of(__float_as_uint(hdr.w) & 0xFFu, sub, tmap, ntab) * a.kpos
                                               : 0);
                 const L2Row R = l2_row<B2>(hdr);
-                accumulate_pair<B1, B2, METRIC, MASK, G, CH, NCH, false>(P, tq, qr, mtab, 0, g, npieces, R, A,
+                accumulate_pair<B1, B2, METRIC, MASK, G, CH, NCH, false, ORD>(P, tq, qr, mtab, &s_zero, 0, g, npieces, R, A,
                                                                          l2acc);
                 for (int p0 = G * NCH; p0 < npieces; p0 += G * NCH) {
                     load_pair<B1, B2, G, CH, NCH>(P, a, e, e1, slot, p0, g, npieces);
-                    accumulate_pair<B1, B2, METRIC, MASK, G, CH, NCH, false>(P, tq, qr, mtab, p0, g, npieces, R,
+                    accumulate_pair<B1, B2, METRIC, MASK, G, CH, NCH, false, ORD>(P, tq, qr, mtab, &s_zero, p0, g, npieces, R,
                                                                              A, l2acc);
                 }
             }
 
-            float score = finish_pair<B2, METRIC, G>(A, l2acc, hdr, cmt, a.n_means, qsum);
+            float score = finish_pair<B2, METRIC, G, NCH, ORD>(A, l2acc, hdr, cmt, a.n_means, qsum);
             if (valid && !work) {
                 score = __uint_as_float(0x7FC00000u);
                 if (g == 0 && !(a.neg_empty && slot < 0)) atomicOr(a.err, kErrBadSlot);

@@ -43,6 +43,13 @@ constexpr CandShape kCandShapes[] = {
     // pipelined, registers allocated for at least six waves per SIMD
     {4, 8, 3, 9},    // 96 bytes
     {2, 16, 3, 9},   // 96 bytes
+    // pipelined, in the order of sums of the 16-lane shapes
+    {4, 8, 2, 25},   // 64 bytes, 16 lanes of 8
+    {4, 8, 3, 25},   // 96 bytes, 16 lanes of 8
+    {4, 8, 4, 25},   // 128 bytes, 16 lanes of 8
+    {4, 16, 2, 17},  // 128 bytes, 16 lanes of 16 (with padding positions)
+    {8, 16, 3, 33},  // 384 bytes, 16 lanes of 8
+    {8, 16, 3, 35},  // 384 bytes, 16 lanes of 8, query in registers
 };
 constexpr int kNumCandShapes = sizeof(kCandShapes) / sizeof(kCandShapes[0]);
 
@@ -51,24 +58,32 @@ using CandKernel = void (*)(CandArgs);
 // variant: 0 = IP, 1 = L2 one mean, 2 = L2 several means, 3 = L2 masked,
 //          4 = L2 masked several means
 // pipe bits: 1 = software-pipelined, 2 = query in registers, 4 = two blocks ahead,
-//            8 = registers for at least six waves per SIMD
+//            8 = registers for at least six waves per SIMD,
+//            16 / 32 = sums in the order kOrdQuads / kOrdHalves
+// Masked (padding positions among the codes): the generic shape, the
+// pipelined 16-lane one with its order of sums, and the 4-lane one with it.
 template <int B1, int B2, int S>
 constexpr CandKernel cand_kernel_for(int variant)
 {
     constexpr CandShape sh = kCandShapes[S];
     constexpr int depth = (sh.pipe & 1) ? ((sh.pipe & 4) ? 2 : 1) : 0;
     constexpr int W = (sh.pipe & 8) ? 6 : 1;
-    switch (variant) {
-    case 0: return k_cand<B1, B2, LVQ_IP, false, false, sh.g, sh.ch, sh.nch, depth, (sh.pipe & 2) != 0, W>;
-    case 1: return k_cand<B1, B2, LVQ_L2, false, false, sh.g, sh.ch, sh.nch, depth, (sh.pipe & 2) != 0, W>;
-    case 2:
-        if constexpr ((sh.pipe & 2) == 0) return k_cand<B1, B2, LVQ_L2, true, false, sh.g, sh.ch, sh.nch, depth, false, W>;
-        return nullptr;
-    default: break;
+    constexpr int O = (sh.pipe & 16) ? kOrdQuads : (sh.pipe & 32) ? kOrdHalves : kOrdLane;
+    constexpr bool masked_only = sh.g == 4 && sh.ch == 16 && O == kOrdQuads;
+    if constexpr (!masked_only) {
+        switch (variant) {
+        case 0: return k_cand<B1, B2, LVQ_IP, false, false, sh.g, sh.ch, sh.nch, depth, (sh.pipe & 2) != 0, W, O>;
+        case 1: return k_cand<B1, B2, LVQ_L2, false, false, sh.g, sh.ch, sh.nch, depth, (sh.pipe & 2) != 0, W, O>;
+        case 2:
+            if constexpr ((sh.pipe & 2) == 0)
+                return k_cand<B1, B2, LVQ_L2, true, false, sh.g, sh.ch, sh.nch, depth, false, W, O>;
+            return nullptr;
+        default: break;
+        }
     }
-    if constexpr (S == 0) {
-        if (variant == 3) return k_cand<B1, B2, LVQ_L2, false, true, sh.g, sh.ch, sh.nch, 0, false, 1>;
-        if (variant == 4) return k_cand<B1, B2, LVQ_L2, true, true, sh.g, sh.ch, sh.nch, 0, false, 1>;
+    if constexpr (S == 0 || S == 10 || masked_only) {
+        if (variant == 3) return k_cand<B1, B2, LVQ_L2, false, true, sh.g, sh.ch, sh.nch, depth, false, 1, O>;
+        if (variant == 4) return k_cand<B1, B2, LVQ_L2, true, true, sh.g, sh.ch, sh.nch, depth, false, 1, O>;
     }
     return nullptr;
 }
@@ -107,6 +122,12 @@ inline CandKernel cand_lookup(int variant, int shape)
     case 27: return B2 == 4 ? nullptr : cand_kernel_for<B1, B2, 27>(variant);
     case 28: return B2 == 4 ? nullptr : cand_kernel_for<B1, B2, 28>(variant);
     case 29: return B2 == 4 ? nullptr : cand_kernel_for<B1, B2, 29>(variant);
+    case 30: return B2 == 4 ? nullptr : cand_kernel_for<B1, B2, 30>(variant);
+    case 31: return B2 == 4 ? nullptr : cand_kernel_for<B1, B2, 31>(variant);
+    case 32: return B2 == 4 ? nullptr : cand_kernel_for<B1, B2, 32>(variant);
+    case 33: return B2 == 4 ? nullptr : cand_kernel_for<B1, B2, 33>(variant);
+    case 34: return B2 == 4 ? nullptr : cand_kernel_for<B1, B2, 34>(variant);
+    case 35: return B2 == 4 ? nullptr : cand_kernel_for<B1, B2, 35>(variant);
     default: return nullptr;
     }
 }

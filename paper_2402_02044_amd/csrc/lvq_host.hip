@@ -271,9 +271,10 @@ int prep_queries(lvq_index *ix, Workspace &w, const float *q, int64_t nq, hipStr
     return prep_into(ix, q, nq, P<float>(w.qk), P<float>(w.qsum), P<float>(w.cm), s);
 }
 
-// Default tile shape: the instantiated shape whose round covers the code
-// bytes with the least waste, preferring more lanes per candidate.
-int default_shape(const Format &f, void *(*lookup)(int, int, int), int bits2, int variant)
+// Order of sums of the default tile shape: that of the shape, among those
+// with an order of their own, whose round covers the code bytes with the
+// least waste, preferring more lanes per candidate.
+int order_shape(const Format &f, void *(*lookup)(int, int, int), int bits2, int variant)
 {
     const int bytes = f.kchunks * 16;
     int best = -1;
@@ -281,6 +282,7 @@ int default_shape(const Format &f, void *(*lookup)(int, int, int), int bits2, in
     for (int i = 0; i < num_tile_shapes(); ++i) {
         if (!lookup(bits2, variant, i)) continue;
         TileShape t = tile_shape(i);
+        if (t.pipe & 48) continue;
         const int round = t.g * t.ch * t.nch;
         const int rounds = (bytes + round - 1) / round;
         if (t.pipe && rounds > 1) continue;
@@ -292,6 +294,52 @@ int default_shape(const Format &f, void *(*lookup)(int, int, int), int bits2, in
         }
     }
     return best;
+}
+
+// Default tile shape: the layout measured fastest among those that give every
+// value with the order of sums of order_shape, so that results do not depend
+// on the choice.  Microseconds for 3.0e6 pairs of 3,000 ragged lists, top-10
+// (the 16-lane shape of that order first, then the layouts compared):
+//   rows of <= 64 B    30: 4-bit d = 128 L2 573 / 137; 4x8 d = 96 IP 711 / 302
+//   rows of <= 96 B    31: 8-bit d = 96 L2 411 / 118, 16 means 391 / 119, IP
+//                      360 / 116 (34: 194, 209, 159); not 4-bit codes at both
+//                      levels, whose four sums per lane spill (698 / 550; 35: 353)
+//   rows of <= 128 B   32 at the first level: 8-bit d = 128 L2 451 / 168 (34:
+//                      200); not 4-bit Euclidean with one mean (580 / 303; 34:
+//                      212), nor both levels (645 / 290; 34: 243)
+//   up to 384 B        34, or 35 (query in registers) where its registers cost
+//                      no occupancy: IP with both levels of 4-bit codes (4x8 d
+//                      = 768 1189 / 561, 34: 578) or 8-bit codes alone (d = 256
+//                      414 / 189, 34: 199), L2 with 8-bit codes alone (d = 256
+//                      465 / 208, 34: 277; but 4x8 d = 768 34: 636, 35: 784)
+//   up to 512 B        18 (query in registers), 10 with several means: 8-bit
+//                      d = 512 IP 551 / 317, L2 529 / 320
+//   padding positions  33 up to 128 B (8-bit d = 100 L2 586 / 137), 10 up to 512
+//                      B (8-bit d = 333 L2 636 / 303)
+// *idle: query slots a lane without a piece multiplied by zero codes in the
+// 16-lane shape (see CandArgs::idle_slots).
+int default_shape(const Format &f, void *(*lookup)(int, int, int), int bits2, int variant, int *idle)
+{
+    const int base = order_shape(f, lookup, bits2, variant);
+    *idle = 0;
+    if (base < 0) return base;
+    const int bytes = f.kchunks * 16;
+    const TileShape t = tile_shape(base);
+    const bool ip = variant == 0, one = variant < 2;
+    int pick = base;
+    if (t.g == 16 && t.ch == 8 && t.nch == 3 && !t.pipe) {
+        const bool b4 = f.bits1 == 4, both = bits2 != 0;
+        if (bytes <= 64) pick = 30;
+        else if (bytes <= 96 && !(b4 && both)) pick = 31;
+        else if (bytes <= 128 && !both && !(b4 && variant == 1)) pick = 32;
+        else pick = one && (ip ? b4 == both : !b4 && !both) ? 35 : 34;
+    } else if (t.g == 16 && t.ch == 16 && t.nch == 2) {
+        if (variant >= 3) pick = bytes <= 128 ? 33 : 10;
+        else pick = one ? 18 : 10;
+    }
+    if (pick == base || !lookup(bits2, variant, pick)) return base;
+    if (ip && bytes < t.g * t.ch * t.nch) *idle = t.ch * 8 / f.bits1;
+    return pick;
 }
 
 bool shape_fits(const Format &f, void *(*lookup)(int, int, int), int bits2, int variant, int shape)
@@ -656,9 +704,10 @@ int lvq::host_distances(lvq_index *ix, const float *q_dev, int64_t nq, const int
     const int variant = !l2 ? 0 : (masked ? (multi ? 4 : 3) : (multi ? 2 : 1));
     auto lookup = f.bits1 == 4 ? cand_kernel_b4 : cand_kernel_b8;
     int shape = force_shape >= 0 ? force_shape : ix->cand_shape[level == LVQ_FULL][k > 0];
+    int idle_slots = 0;
     if (!shape_fits(f, lookup, bits2, variant, shape)) {
         if (force_shape >= 0) return LVQ_ERR_UNSUPPORTED;
-        shape = default_shape(f, lookup, bits2, variant);
+        shape = default_shape(f, lookup, bits2, variant, &idle_slots);
     }
     void *kern = shape >= 0 ? lookup(bits2, variant, shape) : nullptr;
     if (!kern) return LVQ_ERR_UNSUPPORTED;
@@ -728,6 +777,7 @@ int lvq::host_distances(lvq_index *ix, const float *q_dev, int64_t nq, const int
     a.neg_empty = neg_empty ? 1 : 0;
     a.cw = cw;
     a.mu_lds = mu_lds;
+    a.idle_slots = idle_slots;
     a.list_means = (sub || segmented) ? list_means : nullptr;
     a.list_nmeans = (sub || segmented) ? list_nmeans : 0;
     a.seg_offs = segmented ? seg_offs : nullptr;

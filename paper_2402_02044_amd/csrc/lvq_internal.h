@@ -96,6 +96,9 @@ struct CandArgs {
     int neg_empty;           // a negative id is an empty entry, not an error
     int cw;                  // top-k key buffer entries per wave (>= k + 32)
     int mu_lds;              // L2 with several means: keep muk in LDS for the launch
+    int idle_slots;          // IP: the shape whose order of sums is kept had lanes with no piece of the
+                             // row, which multiplied a zero code by the first slots' query values:
+                             // a non-finite one there makes every value NaN (0: no such lanes)
     const int32_t *list_means;   // the means each list's rows belong to (nq x list_nmeans),
     int list_nmeans;             // or NULL for any mean
     const int64_t *seg_offs;     // segmented lists: member ranges per mean (n_means + 1) and the
@@ -145,7 +148,9 @@ struct TileShape {
     int g, ch, nch;   // lanes per candidate, bytes per piece, pieces per lane and round
     int pipe;         // bit 0: software-pipelined single-round candidate loop;
                       // bit 1: query values held in registers for a whole list;
-                      // bit 2: the pipeline runs two blocks of candidates ahead
+                      // bit 2: the pipeline runs two blocks of candidates ahead;
+                      // bit 3: registers for at least six waves per SIMD;
+                      // bits 4, 5: sums in the order of 16 lanes per candidate
 };
 int num_tile_shapes();
 TileShape tile_shape(int i);

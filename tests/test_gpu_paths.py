@@ -76,3 +76,54 @@ def test_topk_merge_edges(L, metric_ip, prec, nq, k):
     np.testing.assert_array_equal(ti.cpu().numpy(), ids)
     np.testing.assert_array_equal(td.cpu().numpy().astype(np.float64), val)
     ix.close()
+
+
+ORDER_CASES = [  # dim, b1, b2, layout (1 turbo), ip, means
+    (96, 8, 0, 0, 0, 1), (96, 8, 0, 0, 0, 16), (96, 8, 0, 0, 1, 1), (100, 8, 0, 0, 0, 1), (100, 8, 0, 0, 0, 5),
+    (100, 8, 0, 0, 1, 3), (128, 8, 0, 0, 0, 1), (96, 4, 0, 1, 0, 1), (96, 4, 0, 0, 1, 1), (96, 4, 8, 1, 1, 2),
+    (96, 4, 8, 1, 0, 1), (120, 8, 8, 0, 1, 1), (192, 4, 8, 0, 0, 4), (192, 4, 0, 0, 1, 1), (256, 4, 0, 0, 0, 1),
+    (256, 4, 0, 0, 0, 3), (333, 8, 0, 0, 0, 1), (333, 8, 8, 0, 1, 1), (333, 4, 8, 0, 1, 1), (768, 4, 8, 1, 1, 1),
+    (768, 4, 8, 1, 0, 2), (500, 8, 0, 0, 1, 1), (512, 8, 0, 1, 0, 1), (512, 8, 8, 1, 0, 2), (17, 8, 4, 0, 1, 1),
+    (730, 4, 0, 0, 1, 1),
+]
+
+
+@pytest.mark.parametrize("d,b1,b2,layout,ip,M", ORDER_CASES)
+def test_default_shape_keeps_order_of_sums(L, d, b1, b2, layout, ip, M):
+    """The default tile shape gives bit for bit what the 16-lane shape of its
+    order of sums gives, for finite and non-finite queries (an infinite
+    component in the first, a later and the last slot, a NaN), and the same
+    top-k."""
+    g = synth.rng(7300 + d, b1 + b2 + M)
+    n, nq = 700, 9
+    X = g.standard_normal((n, d)).astype(np.float32)
+    Q = g.standard_normal((nq, d)).astype(np.float32)
+    Q[3, 0], Q[4, d // 2], Q[5, d - 1], Q[6, d // 3] = np.inf, -np.inf, np.inf, np.nan
+    Q[7, 9] = np.inf
+    means = X[:M] * 0.5
+    ix = L.Index(d, b1, b2, L.LVQ_IP if ip else L.LVQ_L2, layout, capacity=n, means=means)
+    ix.insert(torch.from_numpy(X).cuda())
+    lens = np.array([0, 1, 3, 64, 65, 130, 257, 700, 31])
+    offs = np.concatenate([[0], np.cumsum(lens)])
+    ids = np.concatenate([g.permutation(n)[:m] for m in lens]).astype(np.int32)
+    args = (torch.from_numpy(Q).cuda(), torch.from_numpy(offs).cuda(), torch.from_numpy(ids).cuda())
+    kbytes = -(-ix.code_positions * b1 // 8 // 16) * 16
+    kpos = kbytes * 8 // b1
+    # the 16-lane shape: generic where positions pad the row or residual codes
+    # have 4 bits, else pieces of 8 bytes up to 384 B and of 16 up to 512 B
+    base = 0 if (not ip and kpos != d) or kbytes > 512 else 1 if kbytes <= 384 else 4
+    for level in ([L.LVQ_PRIMARY, L.LVQ_FULL] if b2 else [L.LVQ_PRIMARY]):
+        want = 0 if level == L.LVQ_FULL and b2 == 4 else base
+        for k in (0, 10):
+            got = ix.distances(*args, level=level, k=k)
+            ix.set_tile(level, k > 0, want)
+            ref = ix.distances(*args, level=level, k=k)
+            ix.set_tile(level, k > 0, -1)
+            assert ix.sync() == 0
+            a, b = got[0].cpu().numpy(), ref[0].cpu().numpy()
+            np.testing.assert_array_equal(np.isnan(a), np.isnan(b))
+            ok = ~np.isnan(a)
+            np.testing.assert_array_equal(a.view(np.uint32)[ok], b.view(np.uint32)[ok])
+            if k:
+                assert torch.equal(got[1], ref[1])
+    ix.close()
