@@ -217,7 +217,8 @@ int lvq_tile_shape(int32_t shape, int32_t *lanes, int32_t *piece_bytes, int32_t 
  * for nq queries q_dev (nq x dim) of precision prec at `level`: LVQ_FP32
  * takes float queries and FP32 products -- on the FP32 matrix cores
  * (v_mfma_f32_32x32x2_f32, codes converted exactly) for the first-level inner
- * product of an index with one mean and k <= 512, else on the vector ALUs;
+ * product of an index with one mean and k <= 512, else on the vector ALUs
+ * (which take small batches of those too, with the same values);
  * LVQ_BF16 / LVQ_FP16 take queries already in that type and run matrix-core
  * (MFMA) products of queries and exactly converted integer codes with FP32
  * accumulation (inner product; both levels need 8-bit residual codes).

@@ -246,6 +246,54 @@ __device__ __forceinline__ int wave_sort_compact_e(uint64_t *buf, int n, int k)
     return valid < k ? valid : k;
 }
 
+// One wave folds the pend keys appended at rq[KS + poff ..] into query
+// region rq's sorted KS = 64*E best (rq[0 .. KS)), 64 at a time: the chunk is sorted,
+// reversed and compared position-wise with the last 64 of the sorted list
+// (the half-cleaner of the bitonic sequence list ++ reversed chunk, whose
+// lower half is the KS smallest of both), then merged.  The list goes back to
+// rq[0..KS); when out is set, its first k keys go there too.  Returns the
+// number of valid keys among the first k; *kth receives the k-th.
+template <int E>
+__device__ __forceinline__ int merge_region(uint64_t *rq, int poff, int pend, int k, uint64_t *out, uint64_t *kth)
+{
+    constexpr int KS = 64 * E;
+    const int lane = threadIdx.x & 63;
+    uint64_t top[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) top[e] = rq[e * 64 + lane];
+    for (int c = 0; c < pend; c += 64) {
+        uint64_t x[1] = {c + lane < pend ? rq[KS + poff + c + lane] : kNoKey};
+        wave_bitonic_sort<1>(x);
+        const uint64_t xr = shfl_u64(x[0], 63 - lane);
+        top[E - 1] = xr < top[E - 1] ? xr : top[E - 1];
+        wave_bitonic_merge<E>(top);
+    }
+    int valid = 0;
+    uint64_t kk = kNoKey;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = e * 64 + lane;
+        rq[i] = top[e];
+        if (i < k) {
+            if (out) out[i] = top[e];
+            valid += top[e] != kNoKey;
+        }
+        if (i == k - 1) kk = top[e];
+    }
+    *kth = readlane_u64(kk, (k - 1) & 63);
+    return wave_sum_i32(valid);
+}
+
+__device__ __forceinline__ int merge_region_ks(int ks, uint64_t *rq, int poff, int pend, int k, uint64_t *out,
+                                               uint64_t *kth)
+{
+    if (ks == 64) return merge_region<1>(rq, poff, pend, k, out, kth);
+    if (ks == 128) return merge_region<2>(rq, poff, pend, k, out, kth);
+    if (ks == 256) return merge_region<4>(rq, poff, pend, k, out, kth);
+    if (ks == 512) return merge_region<8>(rq, poff, pend, k, out, kth);
+    return merge_region<16>(rq, poff, pend, k, out, kth);
+}
+
 // Keep the k smallest of buf[0..n) (ascending) in buf[0..k) and return how
 // many are valid keys (< k when fewer survive).  One whole wavefront.
 __device__ __forceinline__ int wave_compact(uint64_t *buf, int n, int k, uint64_t *scratch)

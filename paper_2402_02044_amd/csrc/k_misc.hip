@@ -44,6 +44,52 @@ __global__ __launch_bounds__(256) void k_prep(PrepArgs a)
     }
 }
 
+// The vector scan's queries (see launch_prep_rows): a lane per value below
+// tab_blocks, then a wave per (query, four means) for the sums.
+__global__ __launch_bounds__(256) void k_prep_rows(PrepArgs a, const float *muk, int tq, int pair_chunk, unsigned tab_blocks,
+                                                   int64_t n_tab, uint32_t *gthr)
+{
+    const float *q = reinterpret_cast<const float *>(a.q);
+    if (blockIdx.x < tab_blocks) {
+        const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+        if (e >= n_tab) return;
+        const int64_t i = e / ((int64_t)a.kpos * tq) * tq + e % tq;
+        int p = (int)(e / tq % a.kpos);
+        if (pair_chunk) {
+            const int r = p % pair_chunk;
+            p = p - r + (r & 1) * (pair_chunk / 2) + (r >> 1);
+        }
+        const int j = a.kdim[p];
+        float v = 0.0f;
+        if (i < a.nq) {
+            if (j >= 0) v = q[i * a.dim + j];
+            if (a.metric == LVQ_L2) v -= muk[p];
+            if (p == 0) gthr[i] = 0xFFFFFFFFu;
+        }
+        a.qk[e] = v;
+        return;
+    }
+    const int groups = (a.n_means + 3) / 4, lane = threadIdx.x & 63;
+    const int64_t unit = (int64_t)(blockIdx.x - tab_blocks) * 4 + (threadIdx.x >> 6);
+    const int64_t i = unit / groups;
+    const int m0 = (int)(unit % groups) * 4;
+    if (i >= a.nq) return;
+    q += i * a.dim;
+    if (m0 == 0) {
+        float s = 0.0f;
+        for (int j = lane; j < a.dim; j += 64) s += q[j];
+        s = wave_sum_f32(s);
+        if (lane == 0) a.qsum[i] = s;
+    }
+    for (int m = m0; m < min(m0 + 4, a.n_means); ++m) {
+        const float *mu = a.means + (int64_t)m * a.dim;
+        float s = 0.0f;
+        for (int j = lane; j < a.dim; j += 64) s = fmaf(q[j], mu[j], s);
+        s = wave_sum_f32(s);
+        if (lane == 0) a.cm[i * a.n_means + m] = s;
+    }
+}
+
 __global__ void k_fill_i32(int32_t *p, int32_t v, int64_t n)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -507,6 +553,18 @@ hipError_t launch_prep(const PrepArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
+hipError_t launch_prep_rows(const PrepArgs &a, const float *muk, int tq, int pair_chunk, uint32_t *gthr,
+                            hipStream_t s)
+{
+    if (a.nq <= 0) return hipSuccess;
+    const int64_t n_tab = (a.nq + tq - 1) / tq * tq * a.kpos;
+    const int64_t tb = (n_tab + 255) / 256;
+    const int64_t sb = a.metric == LVQ_IP ? (a.nq * ((a.n_means + 3) / 4) + 3) / 4 : 0;
+    hipLaunchKernelGGL(k_prep_rows, dim3((unsigned)(tb + sb)), dim3(256), 0, s, a, muk, tq, pair_chunk, (unsigned)tb,
+                       n_tab, gthr);
+    return hipGetLastError();
+}
+
 static unsigned fill_blocks(int64_t n)
 {
     int64_t b = (n + 255) / 256;
@@ -656,14 +714,11 @@ size_t cand_lds_bytes(int kpos, int ntab, bool mask, int n_means_ip, int k, int 
 {
     return cand_lds_bytes_impl(kpos, ntab, mask, n_means_ip, k, cw, map, nseg);
 }
-size_t scan_lds_bytes(int kpos, int n_means_ip, int k, int capq)
+int scan_tile_queries(int g, int ch, int bits1, bool few) { return few ? kScanTQSmall : scan_tq(g, ch, bits1); }
+int scan_sorted_keys(int k) { return scan_sorted(k); }
+size_t scan_lds_bytes(int tq, int n_means_ip, int k, int g, int bits1, int bits2)
 {
-    return scan_lds_bytes_impl(kpos, n_means_ip, k, capq);
+    return scan_lds_bytes_impl(tq, (n_means_ip + 3) & ~3, k, scan_staged(g) ? scan_slab(g, bits1, bits2) * (bits1 + bits2) / bits1 : 0);
 }
-int scan_capq(int kpos, int n_means_ip, int k, int rows_per_round, size_t lds_max)
-{
-    return scan_capq_impl(kpos, n_means_ip, k, rows_per_round, lds_max);
-}
-int scan_rows_per_round(int g) { return 256 / g * kScanR; }
 
 }  // namespace lvq

@@ -3,13 +3,18 @@
 
 namespace lvq {
 
-void *scan_kernel_b8(int bits2, int variant, int shape)
+void *scan_kernel_b8(int bits2, int variant, int shape, bool few)
 {
     ScanKernel k = nullptr;
-    if (bits2 == 0) k = scan_lookup<8, 0>(variant, shape);
-    else if (bits2 == 4) k = scan_lookup<8, 4>(variant, shape);
-    else if (bits2 == 8) k = scan_lookup<8, 8>(variant, shape);
+    if (bits2 == 0) k = scan_lookup<8, 0>(variant, shape, few);
+    else if (bits2 == 4) k = scan_lookup<8, 4>(variant, shape, few);
+    else if (bits2 == 8) k = scan_lookup<8, 8>(variant, shape, few);
     return reinterpret_cast<void *>(k);
+}
+
+void *scan_pairs_kernel_b8(int bits2, bool few)
+{
+    return reinterpret_cast<void *>(scan_pairs_lookup<8>(bits2, few));
 }
 
 }  // namespace lvq

@@ -241,8 +241,7 @@ int timing_end(lvq_index *ix, hipStream_t s)
     return LVQ_OK;
 }
 
-// Query prep into the given buffers (nq x kpos, nq, nq x n_means floats).
-int prep_into(lvq_index *ix, const float *q, int64_t nq, float *qk, float *qsum, float *cm, hipStream_t s)
+PrepArgs prep_args(lvq_index *ix, const float *q, int64_t nq, float *qk, float *qsum, float *cm)
 {
     const Format &f = ix->f;
     PrepArgs pa;
@@ -257,7 +256,13 @@ int prep_into(lvq_index *ix, const float *q, int64_t nq, float *qk, float *qsum,
     pa.qk = qk;
     pa.qsum = qsum;
     pa.cm = cm;
-    LVQ_HIP(launch_prep(pa, s));
+    return pa;
+}
+
+// Query prep into the given buffers (nq x kpos, nq, nq x n_means floats).
+int prep_into(lvq_index *ix, const float *q, int64_t nq, float *qk, float *qsum, float *cm, hipStream_t s)
+{
+    LVQ_HIP(launch_prep(prep_args(ix, q, nq, qk, qsum, cm), s));
     return LVQ_OK;
 }
 
@@ -898,15 +903,119 @@ int lvq_autotune(lvq_index *ix, const float *q_dev, int64_t nq, const int64_t *o
 static int topk_mfma(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq, int32_t k, int32_t level,
                      int32_t *ids_dev, float *dist_dev, hipStream_t s, uint32_t epoch);
 
-// Row parts of the FP32 scan: enough workgroups (query tiles x parts) for
-// about four per compute unit, parts of at least 1024 rows, and a merge that
-// holds parts * k keys (+ k) of 8 bytes in one workgroup's LDS.
-static int64_t scan_parts_fp32(const lvq_index *ix, int64_t nq, int32_t k, int64_t n_rows)
+constexpr int64_t kPairsMaxQueries = 8;
+
+// The FP32 vector scan of a format: the kernel that processes a whole row in
+// one round with the least padding, and whether it takes nq queries at this k.
+struct ScanPlan {
+    void *kern = nullptr;
+    int tq = 0;           // queries per tile
+    int pair_chunk = 0;   // positions of a matrix-core chunk, in that order of sums
+    size_t lds = 0;
+    int64_t slots = 0;    // workgroups resident at once
+};
+
+static void scan_slots(const lvq_index *ix, ScanPlan *p)
 {
-    const int64_t qtiles = (nq + 15) / 16;
-    int64_t parts = std::max<int64_t>(1, (4 * (int64_t)ix->n_cu + qtiles - 1) / qtiles);
-    parts = std::min<int64_t>(parts, std::max<int64_t>(1, n_rows / 1024));
-    return std::min<int64_t>(parts, std::max<int64_t>(1, (int64_t)(ix->lds_max / 8 - k) / k));
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, p->kern, 256, p->lds) != hipSuccess || per_cu < 1)
+        per_cu = 1;
+    p->slots = (int64_t)ix->n_cu * per_cu;
+}
+
+// Few FP32 queries, inner product, of a format the wide matrix-core kernel
+// takes: the vector scan in that kernel's order of sums (the same values).
+// The matrix cores work on 32 queries at a time, whatever the batch: over 10^6
+// 4x8 rows of d = 768, both levels, 687 us for one query, 713 for four, 841 for
+// eight; this 311, 382 and 610 us (its vector work grows with every query: past
+// eight, a second tile reads the rows again).
+static bool scan_plan_pairs(const lvq_index *ix, int64_t nq, int32_t k, int32_t level, ScanPlan *p)
+{
+    const Format &f = ix->f;
+    const int bits2 = level == LVQ_FULL ? f.bits2 : 0;
+    if (nq > kPairsMaxQueries || ix->cfg.metric != LVQ_IP) return false;
+    const bool few = 2 * nq <= scan_tile_queries(1, 16, f.bits1, false);
+    p->kern = (f.bits1 == 4 ? scan_pairs_kernel_b4 : scan_pairs_kernel_b8)(bits2, few);
+    p->tq = scan_tile_queries(1, 16, f.bits1, few);
+    p->lds = scan_lds_bytes(p->tq, ix->n_means, k, 1, f.bits1, bits2);
+    p->pair_chunk = f.bits1 == 4 ? 64 : 32;
+    if (!p->kern || p->lds > ix->lds_max) {
+        p->kern = nullptr;
+        return false;
+    }
+    scan_slots(ix, p);
+    return true;
+}
+
+static bool scan_plan(const lvq_index *ix, int64_t nq, int32_t k, int32_t level, ScanPlan *p)
+{
+    const Format &f = ix->f;
+    const bool l2 = ix->cfg.metric == LVQ_L2;
+    const int variant = !l2 ? 0 : (f.kpos != f.dim ? 2 : 1);
+    const int bits2 = level == LVQ_FULL ? f.bits2 : 0;
+    const int nm = l2 ? 0 : ix->n_means;
+    auto lookup = f.bits1 == 4 ? scan_kernel_b4 : scan_kernel_b8;
+    int shape = -1;
+    for (int i = 0; i < num_tile_shapes(); ++i) {
+        if (!lookup(bits2, variant, i, false)) continue;
+        TileShape t = tile_shape(i);
+        if (t.g * t.ch * t.nch < f.kchunks * 16) continue;
+        if (shape < 0) { shape = i; continue; }
+        TileShape b = tile_shape(shape);
+        if (t.g * t.ch * t.nch < b.g * b.ch * b.nch) shape = i;
+    }
+    if (shape < 0) return false;
+    // the largest k taken: 16 queries of kpos values and of k + 512 / g rows'
+    // keys, c_m and 4 k keys of scratch within one workgroup's LDS
+    const size_t need = (size_t)16 * f.kpos * 4 + (((size_t)16 * (((nm + 1) & ~1) + 2) * 4 + 15) & ~(size_t)15) + 256 +
+                        ((size_t)16 * (k + 512 / tile_shape(shape).g) + 4 * (size_t)k) * 8;
+    if (need > ix->lds_max) return false;
+    // few queries take tiles of four (over 300,000 rows of d = 96, 256 workgroups:
+    // one query 55 us, eight 102 us, a tile of sixteen 191 us), and so do key
+    // lists too long for a full tile's LDS
+    const int g = tile_shape(shape).g, ch = tile_shape(shape).ch;
+    const int full = scan_tile_queries(g, ch, f.bits1, false);
+    const bool few = 2 * nq <= full || scan_lds_bytes(full, nm, k, g, f.bits1, bits2) > ix->lds_max;
+    p->tq = scan_tile_queries(g, ch, f.bits1, few);
+    p->lds = scan_lds_bytes(p->tq, nm, k, g, f.bits1, bits2);
+    if (p->lds > ix->lds_max) return false;
+    p->kern = lookup(bits2, variant, shape, few);
+    p->pair_chunk = 0;
+    scan_slots(ix, p);
+    return true;
+}
+
+// Row parts of the FP32 vector scan: the count with the least modelled time, in
+// rows of one workgroup.  A compute unit runs its c = workgroups / units at
+// once up to the resident ones; they share its vector ALUs, so the time is c
+// times one's rows, more where too few are resident to hide each other's
+// loads (600 queries over 300,000 rows of d = 96: one per unit 1,908 us, two
+// 1,136, three 970).  A part costs about three rounds of rows more (its first
+// rounds append nearly every row), and at the end k keys in the merge, whose
+// time does not grow with the row: about k / 4 rows of d = 96 (a tenth of the
+// keys where lists are folded whole, k > 64).  One query, top-10: d = 96,
+// 300,000 rows 55 us with 256 parts, 67 with 512, 117 with 1,024; 4x8 d = 768 204,
+// 182 and 223 us.  Parts of at least one round, and at most 20,480 keys to
+// merge per query.
+static int64_t scan_parts_fp32(const lvq_index *ix, const ScanPlan &pl, int64_t nq, int32_t k, int64_t n_rows)
+{
+    const double merge = (k <= 64 ? 0.25 : 0.1) * k * 96.0 / ix->f.kpos;
+    const int64_t qtiles = (nq + pl.tq - 1) / pl.tq, occ = std::max<int64_t>(1, pl.slots / ix->n_cu);
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>({n_rows / 256, (int64_t)(ix->lds_max / 8 - k) / k,
+                                                                 2 * pl.slots / qtiles + 1}));
+    auto shared = [](int64_t c) { return (double)c * (c == 1 ? 1.77 : c == 2 ? 1.14 : 1.0); };
+    int64_t parts = 1;
+    double best = 0.0;
+    for (int64_t p = 1; p <= most; ++p) {
+        const int64_t c = (qtiles * p + ix->n_cu - 1) / ix->n_cu;
+        const double cost = ((double)(c / occ) * shared(occ) + shared(c % occ)) *
+                            ((double)((n_rows + p - 1) / p) + 768.0) + merge * (double)p;
+        if (p == 1 || cost < best) {
+            best = cost;
+            parts = p;
+        }
+    }
+    return parts;
 }
 
 // Row parts of the MFMA scan (one resident workgroup per compute unit).
@@ -982,45 +1091,34 @@ int lvq::host_topk(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq, i
     if (prec == LVQ_BF16 || prec == LVQ_FP16)
         return topk_mfma(ix, q_dev, prec, nq, k, level, ids_dev, dist_dev, s, epoch);
     const bool l2 = ix->cfg.metric == LVQ_L2;
+    ScanPlan pl;
     // the inner product runs on the FP32 matrix cores when the format, k and
     // the means' c_m table allow
     // (LVQ_FP32_VALU: the vector path whatever the format)
     if (prec == LVQ_FP32 && !l2 &&
         mfma_wide_query_block(f.bits1, level == LVQ_FULL ? f.bits2 : 0, f.kpos, LVQ_FP32, k, ix->n_means,
-                              ix->lds_max))
-        return topk_mfma(ix, q_dev, LVQ_FP32, nq, k, level, ids_dev, dist_dev, s, epoch);
-    if (l2 && ix->n_means > 1) return LVQ_ERR_UNSUPPORTED;
-    const bool masked = l2 && f.kpos != f.dim;
-    const int variant = !l2 ? 0 : (masked ? 2 : 1);
-    const int bits2 = level == LVQ_FULL ? f.bits2 : 0;
-    auto lookup = f.bits1 == 4 ? scan_kernel_b4 : scan_kernel_b8;
-    // a scan processes the whole row in one round
-    int shape = -1;
-    for (int i = 0; i < num_tile_shapes(); ++i) {
-        if (!lookup(bits2, variant, i)) continue;
-        TileShape t = tile_shape(i);
-        if (t.g * t.ch * t.nch < f.kchunks * 16) continue;
-        if (shape < 0) { shape = i; continue; }
-        TileShape b = tile_shape(shape);
-        if (t.g * t.ch * t.nch < b.g * b.ch * b.nch) shape = i;
+                              ix->lds_max)) {
+        if (!scan_plan_pairs(ix, nq, k, level, &pl))
+            return topk_mfma(ix, q_dev, LVQ_FP32, nq, k, level, ids_dev, dist_dev, s, epoch);
     }
-    if (shape < 0) return LVQ_ERR_UNSUPPORTED;
-    void *kern = lookup(bits2, variant, shape);
-    const TileShape sh = tile_shape(shape);
-    const int rpr = scan_rows_per_round(sh.g);
-    const int capq = scan_capq(f.kpos, l2 ? 0 : ix->n_means, k, rpr, ix->lds_max);
-    if (!capq) return LVQ_ERR_UNSUPPORTED;
-    const size_t lds = scan_lds_bytes(f.kpos, l2 ? 0 : ix->n_means, k, capq);
+    if (l2 && ix->n_means > 1) return LVQ_ERR_UNSUPPORTED;
+    if (!pl.kern && !scan_plan(ix, nq, k, level, &pl)) return LVQ_ERR_UNSUPPORTED;
 
     int rc = order_after_updates(ix, s);
     if (rc) return rc;
     Workspace &w = workspace(ix, s);
-    if ((rc = prep_queries(ix, w, (const float *)q_dev, nq, s))) return rc;
+    const int tq = pl.tq;
+    const int64_t qtiles = (nq + tq - 1) / tq;
     const int64_t n_rows = ix->list_len;
-    const int64_t qtiles = (nq + 15) / 16;
-    const int64_t parts = scan_parts_fp32(ix, nq, k, n_rows);
+    const int64_t parts = scan_parts_fp32(ix, pl, nq, k, n_rows);
     const int64_t rows_per_part = std::max<int64_t>(1, (n_rows + parts - 1) / parts);
+    if ((rc = dev_alloc(ix, w.qk, sizeof(float) * (size_t)qtiles * tq * f.kpos))) return rc;
+    if ((rc = dev_alloc(ix, w.qsum, sizeof(float) * (size_t)nq))) return rc;
+    if ((rc = dev_alloc(ix, w.cm, sizeof(float) * (size_t)nq * ix->n_means))) return rc;
+    if ((rc = dev_alloc(ix, w.gthr, sizeof(uint32_t) * (size_t)nq))) return rc;
     if ((rc = dev_alloc(ix, w.part, sizeof(uint64_t) * (size_t)nq * parts * k))) return rc;
+    LVQ_HIP(launch_prep_rows(prep_args(ix, (const float *)q_dev, nq, P<float>(w.qk), P<float>(w.qsum), P<float>(w.cm)),
+                             P<float>(ix->muk), tq, pl.pair_chunk, P<uint32_t>(w.gthr), s));
 
     ScanArgs a;
     a.rows = P<uint8_t>(ix->rows);
@@ -1043,16 +1141,17 @@ int lvq::host_topk(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq, i
     a.epoch = epoch;
     a.rows_per_part = rows_per_part;
     a.n_parts = (int)parts;
-    a.capq = capq;
-    a.gthr = nullptr;
+    a.capq = 0;
+    a.gthr = P<uint32_t>(w.gthr);
     a.part_keys = P<uint64_t>(w.part);
     a.err = P<uint32_t>(ix->err);
+    a.mks = scan_sorted_keys(k);
     ix->last_wg = qtiles * parts;
     ix->last_lists = 0;
     ix->last_parts = (int32_t)parts;
     if ((rc = timing_begin(ix, s))) return rc;
-    hipLaunchKernelGGL(reinterpret_cast<void (*)(ScanArgs)>(kern), dim3((unsigned)qtiles, (unsigned)parts), dim3(256),
-                       lds, s, a);
+    hipLaunchKernelGGL(reinterpret_cast<void (*)(ScanArgs)>(pl.kern), dim3((unsigned)qtiles, (unsigned)parts),
+                       dim3(256), pl.lds, s, a);
     LVQ_HIP(hipGetLastError());
     if ((rc = timing_end(ix, s))) return rc;
     LVQ_HIP(launch_topk_merge(a.part_keys, nq, (int)parts, k, ix->cfg.metric, ids_dev, dist_dev, s));
@@ -1421,10 +1520,19 @@ int lvq::host_reserve(lvq_index *ix, hipStream_t s, int64_t max_nq, int32_t k_fi
     size_t qk = 0, part = 0, q16 = 0, gthr = 0, order = 0, mkeys = 0;
     const size_t qsum = sizeof(float) * (size_t)max_nq;
     const size_t cm = sizeof(float) * (size_t)max_nq * kMaxMeans;   // any mean count the index may reach
-    if (prec == LVQ_FP32 || k_rerank > 0) qk = sizeof(float) * (size_t)max_nq * f.kpos;
+    if (prec == LVQ_FP32 || k_rerank > 0) qk = sizeof(float) * (size_t)((max_nq + 15) / 16 * 16) * f.kpos;
     if (prec == LVQ_FP32) {
-        for (int64_t nq = 1; nq <= max_nq; ++nq)
-            part = std::max(part, sizeof(uint64_t) * (size_t)(nq * scan_parts_fp32(ix, nq, k_first, n_rows) * k_first));
+        gthr = sizeof(uint32_t) * (size_t)max_nq;
+        // (the vector scan's tile size changes once with the batch size)
+        ScanPlan pl, pp;
+        bool have = false;
+        for (int64_t nq = 1; nq <= max_nq; ++nq) {
+            if (nq <= 9) have = scan_plan(ix, nq, k_first, scan_level, &pl);
+            if (scan_plan_pairs(ix, nq, k_first, scan_level, &pp))
+                part = std::max(part, sizeof(uint64_t) * (size_t)(nq * scan_parts_fp32(ix, pp, nq, k_first, n_rows) * k_first));
+            if (have)
+                part = std::max(part, sizeof(uint64_t) * (size_t)(nq * scan_parts_fp32(ix, pl, nq, k_first, n_rows) * k_first));
+        }
         // the FP32 matrix-core scan (inner product; its query block does not
         // depend on the mean count, which only decides whether the c_m table
         // fits)
@@ -1441,7 +1549,6 @@ int lvq::host_reserve(lvq_index *ix, hipStream_t s, int64_t max_nq, int32_t k_fi
                 part = std::max(part, sizeof(uint64_t) * (size_t)(nq * parts * k_first));
                 mkeys = std::max(mkeys, sizeof(uint64_t) * (size_t)grid * tq * mfma_wide_cap(k_first));
             }
-            gthr = sizeof(uint32_t) * (size_t)max_nq;
         }
     } else {
         const int bits2 = scan_level == LVQ_FULL ? f.bits2 : 0;

@@ -140,6 +140,12 @@ struct StoreArgs {
 
 hipError_t launch_encode(const EncodeArgs &a, hipStream_t s);
 hipError_t launch_prep(const PrepArgs &a, hipStream_t s);
+// The vector scan's queries: tiles of tq queries as [position][query] (L2:
+// less the mean muk; zero past nq) into a.qk, a.qsum and a.cm as launch_prep
+// (IP), and the shared bounds gthr reset.  pair_chunk: 0, or the positions of a
+// matrix-core chunk, whose two halves are then interleaved.
+hipError_t launch_prep_rows(const PrepArgs &a, const float *muk, int tq, int pair_chunk, uint32_t *gthr,
+                            hipStream_t s);
 // Kernel tables: k_cand / k_scan instantiations by first-level width, level
 // residual width (0 at the first level), variant and tile shape; nullptr when
 // not instantiated.  cand variants: 0 IP, 1 L2, 2 L2 several means, 3 L2
@@ -156,13 +162,18 @@ int num_tile_shapes();
 TileShape tile_shape(int i);
 void *cand_kernel_b4(int bits2, int variant, int shape);
 void *cand_kernel_b8(int bits2, int variant, int shape);
-void *scan_kernel_b4(int bits2, int variant, int shape);
-void *scan_kernel_b8(int bits2, int variant, int shape);
+// (few: the scan instantiation with the fewest queries per tile)
+void *scan_kernel_b4(int bits2, int variant, int shape, bool few);
+void *scan_kernel_b8(int bits2, int variant, int shape, bool few);
+// The vector scan in the FP32 matrix cores' order of sums (inner product).
+void *scan_pairs_kernel_b4(int bits2, bool few);
+void *scan_pairs_kernel_b8(int bits2, bool few);
 size_t cand_lds_bytes(int kpos, int ntab, bool mask, int n_means_ip, int k, int cw, bool map = false,
                       int nseg = 0);
-size_t scan_lds_bytes(int kpos, int n_means_ip, int k, int capq);
-int scan_capq(int kpos, int n_means_ip, int k, int rows_per_round, size_t lds_max);
-int scan_rows_per_round(int g);
+// FP32 vector scan: queries per tile, sorted keys kept per query, LDS bytes.
+int scan_tile_queries(int g, int ch, int bits1, bool few);
+int scan_sorted_keys(int k);
+size_t scan_lds_bytes(int tq, int n_means_ip, int k, int g, int bits1, int bits2);
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 // Soft inverted index (k_probe.hip): per-mean member lists of `list`
 // (counts, cursor: n_means entries; offsets: n_means + 1; members: n entries,

@@ -127,3 +127,78 @@ def test_default_shape_keeps_order_of_sums(L, d, b1, b2, layout, ip, M):
             if k:
                 assert torch.equal(got[1], ref[1])
     ix.close()
+
+
+@pytest.mark.parametrize("d,bits,ip", [(96, 8, 0), (100, 8, 0), (128, 8, 0), (520, 8, 0), (40, 4, 0), (512, 4, 0),
+                                       (100, 8, 1), (96, 8, 1), (512, 8, 1), (768, 4, 1)])
+@pytest.mark.parametrize("n", [1, 255, 257, 3001])
+def test_vector_scan_edges(L, d, bits, ip, n):
+    """The FP32 vector scans: query tiles of 4, 8 and 16 whole and ragged, row
+    rounds of 256 whole and ragged, several means (IP), rows of one slab and of
+    many, both orders of sums (IP few queries take the matrix cores', the
+    plain form the leaves')."""
+    g = synth.rng(7500 + d + n, bits + ip)
+    top = 2 ** bits - 1
+    X = g.integers(0, top + 1, (n, d)).astype(np.float32)
+    X[:, 0], X[:, d - 1] = 0.0, top
+    X[n // 2:] = X[g.integers(0, max(1, n // 2), n - n // 2)]
+    Q = int_queries(g, 17, d)
+    M = 3 if ip else 1
+    means = np.zeros((M, d), np.float32)
+    ix = L.Index(d, bits, 0, L.LVQ_IP if ip else L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=n, means=means)
+    ix.insert(torch.from_numpy(X).cuda())
+    dead = np.unique(g.integers(0, n, n // 9))
+    if len(dead):
+        ix.delete(torch.tensor(dead, dtype=torch.int32, device="cuda"))
+    v = values(ip, Q, X).astype(np.float64)
+    v[:, dead] = -np.inf if ip else np.inf
+    for nq in (1, 4, 5, 8, 9, 16, 17):
+        for k in (1, 10, 70):
+            ids, val = best(ip, v[:nq], k)
+            gone = ~np.isfinite(val)
+            ids[gone] = -1
+            for plain in ((False, True) if ip else (False,)):
+                ti, td = ix.topk(torch.from_numpy(Q[:nq]).cuda(), k, plain=plain)
+                assert ix.sync() == 0
+                np.testing.assert_array_equal(ti.cpu().numpy(), ids)
+                np.testing.assert_array_equal(td.cpu().numpy().astype(np.float64), val)
+    ix.close()
+
+
+@pytest.mark.parametrize("d,b1,b2,layout,M", [(96, 8, 0, 0, 1), (128, 4, 8, 1, 3), (512, 8, 8, 0, 1), (768, 4, 8, 1, 16),
+                                              (1024, 4, 0, 0, 2), (384, 4, 0, 1, 1)])
+def test_few_queries_match_batch_bits(L, d, b1, b2, layout, M):
+    """One to eight FP32 inner-product queries (vector ALUs) return, bit for
+    bit, what the same queries return within a batch (matrix cores), a
+    non-finite query included."""
+    g = synth.rng(7700 + d, b1 + b2)
+    n = 2500
+    X = g.standard_normal((n, d)).astype(np.float32)
+    Q = g.standard_normal((40, d)).astype(np.float32)
+    Q[2, d // 2], Q[5, 3] = np.inf, np.nan
+    ix = L.Index(d, b1, b2, L.LVQ_IP, layout, capacity=n, means=X[:M] * 0.3)
+    ix.insert(torch.from_numpy(X).cuda())
+    qd = torch.from_numpy(Q).cuda()
+    for level in ([L.LVQ_PRIMARY, L.LVQ_FULL] if b2 else [L.LVQ_PRIMARY]):
+        ids, val = ix.topk(qd, 20, level=level)
+        for a, b in ((0, 1), (0, 3), (2, 6), (0, 8), (5, 6)):
+            ti, td = ix.topk(qd[a:b].contiguous(), 20, level=level)
+            assert torch.equal(ti, ids[a:b]) and torch.equal(td, val[a:b])
+    assert ix.sync() == 0
+    ix.close()
+
+
+def test_euclidean_nan_queries_rank_by_slot(L):
+    """A NaN query's values are all NaN: the lowest live slots are returned."""
+    g = synth.rng(7800, 0)
+    X = g.standard_normal((700, 96)).astype(np.float32)
+    ix = L.Index(96, 8, 0, L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=700)
+    ix.insert(torch.from_numpy(X).cuda())
+    ix.delete(torch.tensor([1, 4], dtype=torch.int32, device="cuda"))
+    Q = g.standard_normal((20, 96)).astype(np.float32)
+    Q[7, 50] = np.nan
+    for nq in (20, 8):
+        ti, td = ix.topk(torch.from_numpy(Q[-nq:] if nq == 20 else Q[:8]).cuda(), 5)
+        assert ti[7].tolist() == [0, 2, 3, 5, 6] and torch.isnan(td[7]).all()
+        assert not torch.isnan(td[:7]).any()
+    ix.close()
