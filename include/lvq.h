@@ -173,8 +173,8 @@ int lvq_distances(lvq_index *index, const float *q_dev, int64_t nq, const int64_
  * results, except that its scratch -- the queries in kernel order
  * (nq x kpos floats, kpos = code positions rounded up to 16-byte chunks),
  * the sums of q (nq floats), the per-mean terms (nq x n_means floats), the
- * list order (nq int32) and a work counter, each rounded up to 256 bytes --
- * lives in one fixed array of LVQ_NOALLOC_SCRATCH_BYTES per device instead of
+ * list order (nq int32) and a work counter, each rounded up to 256 bytes (or,
+ * for a small batch whose lists are split, their parts' keys) -- lives in one fixed array of LVQ_NOALLOC_SCRATCH_BYTES per device instead of
  * the stream's workspace.  The call allocates nothing and creates no event
  * (with no spare in-flight record it waits for the oldest query launch of
  * the index), and lvq_set_timing does not time it.  The array is set up by
@@ -388,7 +388,8 @@ int lvq_bw_gather(lvq_index *index, const int32_t *ids_dev, int64_t n, int32_t l
  * before the first): last_workgroups is the grid of its main similarity
  * launch, last_lists the lists it scored (lvq_distances, lvq_probe_topk:
  * the persistent workgroups pop lists from a device counter, so a grid
- * smaller than the list count makes workgroups take several lists), and
+ * smaller than the list count makes workgroups take several lists; a small
+ * batch's lists are split over several workgroups each), and
  * last_parts the row parts an exhaustive scan split the occupied slots
  * into (lvq_topk; each part keeps its own top-k, merged afterwards).      */
 typedef struct {

@@ -9,8 +9,10 @@
 //       form: no cancellation for near neighbours)
 //
 // Launch shape.  A workgroup of 256 lanes owns one candidate list at a time
-// (one list per workgroup, or a persistent loop popping lists from a work
-// counter in descending-length order).  A list's query data lives in LDS in a
+// (a persistent loop popping lists from a work counter in descending-length
+// order), or, where a batch leaves workgroups idle, one of several parts of
+// one, whose keys the merge kernel folds.  It prepares the list's query itself
+// (kernel order, sum(q), c_m).  A list's query data lives in LDS in a
 // bank-conflict-free layout; a group of G lanes scores one candidate: its
 // lanes fetch disjoint CH-byte pieces of the row (NCH pieces each, all issued
 // before any is consumed), decode nibbles/bytes with mask + byte conversion,
@@ -494,6 +496,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
     uint64_t *keys = reinterpret_cast<uint64_t *>(sbase + (seg ? nseg + 1 : 0));
     uint64_t *wbuf = keys + (size_t)wave * a.cw;
     uint64_t *merge = keys + (size_t)4 * a.cw;
+    __shared__ float s_qsum;
     __shared__ float4 s_zero;
     if (tid == 0) s_zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // read after the lists' barriers
     __shared__ int s_item;
@@ -512,21 +515,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
             __syncthreads();
             item = s_item;
         } else {
-            item = iter == 0 ? (int)blockIdx.x : (int)a.nq;
+            item = iter == 0 ? (int)blockIdx.x : INT32_MAX;
         }
-        if (item >= a.nq) break;
-        const int64_t list = a.order ? a.order[item] : item;
+        if (item >= a.nq * a.parts) break;
+        const int part = a.parts > 1 ? item % a.parts : 0;
+        const int64_t list = a.order ? a.order[item] : a.parts > 1 ? item / a.parts : item;
         int64_t e0 = a.offsets[list], e1 = a.offsets[list + 1];
         if (e0 < 0 || e1 < e0 || e1 > a.total) {
             if (tid == 0) atomicOr(a.err, kErrBadOffsets);
             e1 = e0 = 0;
         }
+        // this item's entries: whole blocks of them per part
+        int64_t skip = 0;
+        if (a.parts > 1) {
+            const int64_t run = ((e1 - e0 + a.parts - 1) / a.parts + kPairsPerBlock - 1) / kPairsPerBlock * kPairsPerBlock;
+            skip = min(e1 - e0, part * run);
+            e0 += skip;
+            e1 = min(e1, e0 + run);
+        }
 
         // ---- per-list query tables in LDS
         __syncthreads();
-        const float *qk = a.qk + list * a.kpos;
+        const float *qv = a.q ? a.q + list * a.dim : a.qk + list * a.kpos;
         for (int sp = tid; sp < a.kpos; sp += 256) {
-            const float v = qk[sp];
+            float v;
+            if (a.q) {
+                const int j = a.kdim[sp];
+                v = j >= 0 ? qv[j] : 0.0f;
+            } else {
+                v = qv[sp];
+            }
             const int j = qtab_index<B1, CH>(sp, npieces);
             for (int t = 0; t < ntab; ++t) {
                 float w = v;
@@ -538,7 +556,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
         }
         if (MASK)
             for (int sp = tid; sp < a.kpos; sp += 256) mtab[qtab_index<B1, CH>(sp, npieces)] = a.kmask[sp];
-        for (int m = tid; m < cm_n; m += 256) cmt[m] = a.cm[list * a.n_means + m];
+        if constexpr (METRIC == LVQ_IP) {
+            if (a.q) {
+                // sum(q) and c_m (of the list's means where it names them), as
+                // the preparation kernel sums them: a wave each
+                if (wave == 0) {
+                    float s = 0.0f;
+                    for (int j = lane; j < a.dim; j += 64) s += qv[j];
+                    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+                    if (lane == 0) s_qsum = s;
+                }
+                const int nm = a.list_means ? a.list_nmeans : a.n_means;
+                for (int t = wave; t < nm; t += 4) {
+                    const int m = a.list_means ? a.list_means[list * nm + t] : t;
+                    const float *mu = a.means + (int64_t)m * a.dim;
+                    float s = 0.0f;
+                    for (int j = lane; j < a.dim; j += 64) s = fmaf(qv[j], mu[j], s);
+                    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+                    if (lane == 0) cmt[m] = s;
+                }
+            } else {
+                for (int m = tid; m < cm_n; m += 256) cmt[m] = a.cm[list * a.n_means + m];
+                if (tid == 0) s_qsum = a.qsum[list];
+            }
+        }
         if (sub)
             for (int t = tid; t < ntab; t += 256) tmap[a.list_means[list * ntab + t]] = (uint8_t)t;
         if (seg)
@@ -550,12 +591,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
         __syncthreads();
         if (seg) {
             if (tid == 0) {
-                sstart[0] = 0;
+                sstart[0] = -skip;   // (counted from the item's first entry)
                 for (int p = 0; p < nseg; ++p) sstart[p + 1] += sstart[p];
             }
             __syncthreads();
         }
-        float qsum = METRIC == LVQ_IP ? a.qsum[list] : 0.0f;
+        float qsum = METRIC == LVQ_IP ? s_qsum : 0.0f;
         // (see CandArgs::idle_slots: adds 0, or NaN)
         if constexpr (METRIC == LVQ_IP)
             for (int sp = 0; sp < a.idle_slots; ++sp) qsum = fmaf(qtab[qtab_index<B1, CH>(sp, npieces)], 0.0f, qsum);
@@ -695,7 +736,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
                     n += gw;
                 }
                 const int got = wave_compact_lean(merge, n, k, keys);
+                uint64_t *dst = a.parts > 1 ? a.part_keys + (list * a.parts + part) * k : nullptr;
                 for (int i = lane; i < k; i += 64) {
+                    if (dst) {
+                        dst[i] = i < got ? merge[i] : kNoKey;
+                        continue;
+                    }
                     int32_t sid = -1;
                     float sv = METRIC == LVQ_L2 ? __uint_as_float(0x7F800000u) : __uint_as_float(0xFF800000u);
                     if (i < got) {

@@ -67,7 +67,7 @@ constexpr CandKernel cand_kernel_for(int variant)
 {
     constexpr CandShape sh = kCandShapes[S];
     constexpr int depth = (sh.pipe & 1) ? ((sh.pipe & 4) ? 2 : 1) : 0;
-    constexpr int W = (sh.pipe & 8) ? 6 : 1;
+    constexpr int W = (sh.pipe & 8) ? 6 : 2;   // (a few registers over half the file would halve the waves)
     constexpr int O = (sh.pipe & 16) ? kOrdQuads : (sh.pipe & 32) ? kOrdHalves : kOrdLane;
     constexpr bool masked_only = sh.g == 4 && sh.ch == 16 && O == kOrdQuads;
     if constexpr (!masked_only) {

@@ -128,11 +128,14 @@ __global__ void k_cast16(const float *x, int64_t n, int prec, uint16_t *out)
 // Lists are bucketed by floor(log2(length)), longest bucket first, so the
 // work counter hands out long lists before short ones (longest-first
 // scheduling).  The order inside a bucket does not affect any result.
-__global__ __launch_bounds__(1024) void k_list_order(const int64_t *offsets, int64_t nq, int32_t *order)
+// The work counter is reset beside it.
+__global__ __launch_bounds__(1024) void k_list_order(const int64_t *offsets, int64_t nq, int32_t *order,
+                                                     int32_t *queue)
 {
     __shared__ int hist[64];
     __shared__ int base[64];
     const int tid = threadIdx.x;
+    if (tid == 0) *queue = 0;
     if (tid < 64) hist[tid] = 0;
     __syncthreads();
     for (int64_t i = tid; i < nq; i += 1024) {
@@ -614,10 +617,10 @@ hipError_t launch_cast16(const float *x, int64_t n, int prec, void *out, hipStre
     return hipGetLastError();
 }
 
-hipError_t launch_list_order(const int64_t *offsets, int64_t nq, int32_t *order, int32_t *, hipStream_t s)
+hipError_t launch_list_order(const int64_t *offsets, int64_t nq, int32_t *order, int32_t *queue, hipStream_t s)
 {
     if (nq <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_list_order, dim3(1), dim3(1024), 0, s, offsets, nq, order);
+    hipLaunchKernelGGL(k_list_order, dim3(1), dim3(1024), 0, s, offsets, nq, order, queue);
     return hipGetLastError();
 }
 

@@ -743,16 +743,50 @@ int lvq::host_distances(lvq_index *ix, const float *q_dev, int64_t nq, const int
 
     int rc = order_after_updates(ix, s);
     if (rc) return rc;
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, lds) != hipSuccess || per_cu < 1) per_cu = 1;
+    const int64_t slots = (int64_t)ix->n_cu * per_cu;
+    // The kernel prepares each list's query itself, which saves a launch; for
+    // inner products not where many means make that long (a wave sums four of
+    // sixteen), nor where workgroups take several lists and would each wait
+    // for those sums between them (10^4 x 1,000 pairs: 2,129 us, prepared before
+    // 2,049 us).
+    bool prep = !l2 && (list_means ? list_nmeans : ix->n_means) > 16;
+    // A batch that leaves workgroups idle has its lists split: parts of at
+    // least one block of candidates, and more where a part builds many query
+    // tables.  One list of 256 at 4x8 d = 768: 31 us whole, 20 us in
+    // eight parts, merge included; 5,000 entries 323 and 26 us.  (A list whose entries are not counted on
+    // the host is taken as its means' share of the store.)
+    const int ppb = 4 * (64 / tile_shape(shape).g);
+    const double avg = total == INT64_MAX ? (double)ix->list_len * list_nmeans / ix->n_means : (double)total / nq;
+    int parts = (int)std::min<double>((double)(slots / nq), avg / (ppb * (1.0 + ntab * f.kpos / 4096)));
+    Workspace *ws = fixed ? nullptr : &workspace(ix, s);
+    if (k > 0 && parts > 1) {
+        // room for the keys: the fixed scratch, which prepared queries would
+        // occupy; a workspace that may not grow now keeps the lists whole
+        const size_t need = sizeof(uint64_t) * (size_t)slots * k;
+        if (fixed ? prep || need > fixed->bytes : need > ws->part.bytes && (ix->capturing || ws->part.pinned)) parts = 1;
+    }
+    parts = std::max(1, parts);
+    // every item resident at once: no order, no counter
+    const bool queued = nq * parts > slots;
+    prep = prep || (queued && !l2);
     DistScratch sc;
+    uint64_t *part_keys = nullptr;
     if (fixed) {
         sc = *fixed;
-        if ((rc = prep_into(ix, q_dev, nq, sc.qk, sc.qsum, sc.cm, s))) return rc;
+        part_keys = reinterpret_cast<uint64_t *>(sc.all);
+        if (prep && (rc = prep_into(ix, q_dev, nq, sc.qk, sc.qsum, sc.cm, s))) return rc;
     } else {
-        Workspace &w = workspace(ix, s);
-        if ((rc = prep_queries(ix, w, q_dev, nq, s))) return rc;
+        Workspace &w = *ws;
+        if (prep && (rc = prep_queries(ix, w, q_dev, nq, s))) return rc;
         if ((rc = dev_alloc(ix, w.order, sizeof(int32_t) * (size_t)nq))) return rc;
         if ((rc = dev_alloc(ix, w.queue, 64))) return rc;
-        sc = {P<float>(w.qk), P<float>(w.qsum), P<float>(w.cm), P<int32_t>(w.order), P<int32_t>(w.queue)};
+        if (parts > 1 && k > 0) {
+            if ((rc = dev_alloc(ix, w.part, sizeof(uint64_t) * (size_t)slots * k))) return rc;
+            part_keys = P<uint64_t>(w.part);
+        }
+        sc = {P<float>(w.qk), P<float>(w.qsum), P<float>(w.cm), P<int32_t>(w.order), P<int32_t>(w.queue), nullptr, 0};
     }
 
     CandArgs a;
@@ -763,6 +797,10 @@ int lvq::host_distances(lvq_index *ix, const float *q_dev, int64_t nq, const int
     a.kchunks = f.kchunks;
     a.kpos = f.kpos;
     a.capacity = ix->cfg.capacity;
+    a.q = prep ? nullptr : q_dev;
+    a.kdim = P<int32_t>(ix->kdim);
+    a.means = P<float>(ix->means);
+    a.dim = f.dim;
     a.qk = sc.qk;
     a.qsum = sc.qsum;
     a.cm = sc.cm;
@@ -787,21 +825,25 @@ int lvq::host_distances(lvq_index *ix, const float *q_dev, int64_t nq, const int
     a.list_nmeans = (sub || segmented) ? list_nmeans : 0;
     a.seg_offs = segmented ? seg_offs : nullptr;
     a.seg_members = segmented ? seg_members : nullptr;
-    // persistent launch: lists longest-first from a device work counter
-    a.order = sc.order;
-    a.queue = sc.queue;
-    LVQ_HIP(launch_fill_i32(a.queue, 0, 1, s));
-    LVQ_HIP(launch_list_order(offsets_dev, nq, sc.order, nullptr, s));
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, lds) != hipSuccess || per_cu < 1) per_cu = 1;
-    const int64_t grid = std::min<int64_t>(nq, (int64_t)ix->n_cu * per_cu);
+    a.order = queued ? sc.order : nullptr;
+    a.queue = queued ? sc.queue : nullptr;
+    a.parts = parts;
+    a.part_keys = part_keys;
+    if (queued) {
+        // persistent launch: lists longest-first from a device work counter
+        LVQ_HIP(launch_list_order(offsets_dev, nq, sc.order, sc.queue, s));
+    }
+    const int64_t grid = std::min<int64_t>(nq * parts, slots);
     ix->last_wg = grid;
     ix->last_lists = nq;
     ix->last_parts = 0;
     if (!fixed && (rc = timing_begin(ix, s))) return rc;
     hipLaunchKernelGGL(reinterpret_cast<void (*)(CandArgs)>(kern), dim3((unsigned)grid), dim3(256), lds, s, a);
     LVQ_HIP(hipGetLastError());
-    return fixed ? LVQ_OK : timing_end(ix, s);
+    if (!fixed && (rc = timing_end(ix, s))) return rc;
+    if (parts > 1 && k > 0)
+        LVQ_HIP(launch_topk_merge(part_keys, nq, parts, k, ix->cfg.metric, topk_ids_dev, topk_dist_dev, s));
+    return LVQ_OK;
 }
 
 extern "C" {
@@ -1577,7 +1619,11 @@ int lvq::host_reserve(lvq_index *ix, hipStream_t s, int64_t max_nq, int32_t k_fi
         }
         gthr = sizeof(uint32_t) * (size_t)max_nq;
     }
-    if (k_rerank > 0) order = sizeof(int32_t) * (size_t)max_nq;
+    if (k_rerank > 0) {
+        order = sizeof(int32_t) * (size_t)max_nq;
+        // keys of split lists: one item per resident workgroup of 256 lanes
+        part = std::max(part, sizeof(uint64_t) * (size_t)ix->n_cu * 8 * k_rerank);
+    }
     Workspace &w = workspace(ix, s);
     int rc;
     if (qk && (rc = dev_alloc(ix, w.qk, qk))) return rc;

@@ -27,6 +27,8 @@ struct DevBuf {
 struct DistScratch {
     float *qk, *qsum, *cm;
     int32_t *order, *queue;
+    void *all;       // the scratch as a whole and its bytes: keys of split lists
+    size_t bytes;    //   (which use nothing else of it)
 };
 
 // Per-stream scratch of the query entry points.

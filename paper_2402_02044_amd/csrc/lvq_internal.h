@@ -78,6 +78,10 @@ struct CandArgs {
     int row_bytes, resid_bytes;
     int kchunks, kpos;
     int64_t capacity;
+    const float *q;          // nq x dim queries the kernel prepares itself, or NULL: qk, qsum, cm
+    const int32_t *kdim;     //   hold them (kernel order, sum(q), c_m); kdim: dimension per slot
+    const float *means;      //   M x dim
+    int dim;
     const float *qk, *qsum, *cm;
     const float *muk;        // M x kpos means in kernel order (L2)
     const float *kmask;      // kpos: 1 at real positions, 0 at padding (L2)
@@ -92,7 +96,9 @@ struct CandArgs {
     uint32_t epoch;
     uint32_t *err;
     const int32_t *order;    // list processing order (NULL: identity)
-    int32_t *queue;          // persistent work counter (NULL: one list per block)
+    int32_t *queue;          // persistent work counter (NULL: one item per block)
+    int parts;               // items per list (1 with a queue): part p of a list is its p-th run of
+    uint64_t *part_keys;     //   entries; with several, the top-k keys of (list, part) go here
     int neg_empty;           // a negative id is an empty entry, not an error
     int cw;                  // top-k key buffer entries per wave (>= k + 32)
     int mu_lds;              // L2 with several means: keep muk in LDS for the launch
@@ -278,7 +284,8 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_bw_stream(const void *src, int64_t n16, uint32_t *sink, hipStream_t s);
 hipError_t launch_bw_gather(const uint8_t *rows, int row_bytes, int code16, const uint8_t *resid, int resid_bytes,
                             int res16, const int32_t *ids, int64_t n, int64_t capacity, uint32_t *sink, hipStream_t s);
-hipError_t launch_list_order(const int64_t *offsets, int64_t nq, int32_t *order, int32_t *scratch,
+// (the lists longest first into order; *queue is set to 0)
+hipError_t launch_list_order(const int64_t *offsets, int64_t nq, int32_t *order, int32_t *queue,
                              hipStream_t s);
 // bits2: 0 scans the first level, 8 both levels (8-bit residual codes).
 hipError_t launch_scan_mfma(const ScanArgs &a, int bits1, int bits2, int prec, hipStream_t s);

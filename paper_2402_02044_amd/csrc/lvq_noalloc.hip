@@ -72,6 +72,8 @@ extern "C" int lvq_distances_noalloc(lvq_index *ix, const float *q_dev, int64_t 
     sc.cm = reinterpret_cast<float *>(p + b_qk + b_qsum);
     sc.order = reinterpret_cast<int32_t *>(p + b_qk + b_qsum + b_cm);
     sc.queue = reinterpret_cast<int32_t *>(p + b_qk + b_qsum + b_cm + b_order);
+    sc.all = p;
+    sc.bytes = kScratchBytes;
     hipStream_t s = (hipStream_t)stream;
     int rc = host_begin_call(ix, s);
     if (rc) return rc;

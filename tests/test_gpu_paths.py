@@ -202,3 +202,92 @@ def test_euclidean_nan_queries_rank_by_slot(L):
         assert ti[7].tolist() == [0, 2, 3, 5, 6] and torch.isnan(td[7]).all()
         assert not torch.isnan(td[:7]).any()
     ix.close()
+
+
+@pytest.mark.parametrize("d,b1,b2,ip,M", [(96, 8, 0, 0, 4), (96, 8, 0, 1, 1), (768, 4, 8, 1, 16), (200, 4, 8, 0, 1),
+                                          (64, 8, 0, 1, 40)])
+def test_split_lists_match_whole_ones(L, d, b1, b2, ip, M):
+    """Lists split over workgroups (few queries) give the values and the top-k
+    of the same lists within a batch large enough to keep them whole: empty
+    and one-entry lists, duplicates far apart, tombstoned and invalid slots."""
+    g = synth.rng(7900 + d, b1 + M)
+    n = 3000
+    X = g.standard_normal((n, d)).astype(np.float32)
+    ix = L.Index(d, b1, b2, L.LVQ_IP if ip else L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=n, means=X[:M] * 0.4)
+    ix.insert(torch.from_numpy(X).cuda())
+    ix.delete(torch.from_numpy(np.unique(g.integers(0, n, 200)).astype(np.int32)).cuda())
+    lens = [2900, 0, 1, 1700, 33, 5000]
+    lists = [g.integers(0, n, m).astype(np.int32) for m in lens]
+    lists[0][2800:] = lists[0][:100]
+    lists[3][900] = -5
+    Q = g.standard_normal((len(lens), d)).astype(np.float32)
+    level = L.LVQ_FULL if b2 else L.LVQ_PRIMARY
+    small = np.concatenate([[0], np.cumsum(lens)])
+    ids = np.concatenate(lists)
+    reps = 2500   # whole: every list again, 2,500 times as many items, mostly empty ones
+    big_offs = np.concatenate([small, np.full(reps, small[-1])])
+    big_q = np.concatenate([Q, np.zeros((reps, d), np.float32)])
+    for k in (0, 10, 150):
+        a = ix.distances(torch.from_numpy(Q).cuda(), torch.from_numpy(small).cuda(), torch.from_numpy(ids).cuda(),
+                         level=level, k=k)
+        assert ix.stats().last_workgroups > len(lens) and ix.sync() == L.LVQ_ERR_BAD_SLOT
+        b = ix.distances(torch.from_numpy(big_q).cuda(), torch.from_numpy(big_offs).cuda(),
+                         torch.from_numpy(ids).cuda(), level=level, k=k)
+        assert ix.sync() == L.LVQ_ERR_BAD_SLOT
+        assert torch.equal(a[0].nan_to_num(7e30), b[0].nan_to_num(7e30))
+        if k:
+            assert torch.equal(a[1], b[1][:len(lens)]) and torch.equal(a[2], b[2][:len(lens)])
+    ix.close()
+
+
+@pytest.mark.parametrize("ip", [0, 1])
+@pytest.mark.parametrize("M,nprobe", [(5, 2), (60, 20)])
+def test_split_probe_matches_batch(L, ip, M, nprobe):
+    """One query's probed members, split over workgroups, give what the query
+    gets within a batch whose lists stay whole (by the same tile shape)."""
+    g = synth.rng(7950 + M, ip)
+    n, d = 6000, 96
+    X = g.standard_normal((n, d)).astype(np.float32)
+    ix = L.Index(d, 8, 0, L.LVQ_IP if ip else L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=n, means=X[:M])
+    ix.insert(torch.from_numpy(X).cuda())
+    Q = torch.from_numpy(g.standard_normal((2500, d)).astype(np.float32)).cuda()
+    whole = ix.probe_topk(Q, nprobe, 12)
+    for i in (0, 7):
+        one = ix.probe_topk(Q[i:i + 1].contiguous(), nprobe, 12)
+        assert ix.stats().last_workgroups > 1
+        for a, b in zip(one, whole):
+            assert torch.equal(a, b[i:i + 1])
+    assert ix.sync() == 0
+    ix.close()
+
+
+def test_split_lists_under_capture(L):
+    """A captured call whose workspace has no room for split lists' keys keeps
+    them whole; one that has it replays the split."""
+    g = synth.rng(7990, 0)
+    n, d = 2000, 96
+    X = g.standard_normal((n, d)).astype(np.float32)
+    ix = L.Index(d, 8, 0, L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=n)
+    ix.insert(torch.from_numpy(X).cuda())
+    q = torch.from_numpy(g.standard_normal((2, d)).astype(np.float32)).cuda()
+    offs = torch.tensor([0, 1500, 2000], device="cuda")
+    ids = torch.from_numpy(g.permutation(n).astype(np.int32)).cuda()
+    want = ix.distances(q, offs, ids, k=9)
+    s = torch.cuda.Stream()
+    for warm_k in (0, 9):
+        with torch.cuda.stream(s):
+            ix.distances(q, offs, ids, k=warm_k)
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            got = ix.distances(q, offs, ids, k=9)
+        for _ in range(3):
+            for t in got:
+                t.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            for a, b in zip(got, want):
+                assert torch.equal(a, b)
+        s = torch.cuda.Stream()
+    assert ix.sync() == 0
+    ix.close()
