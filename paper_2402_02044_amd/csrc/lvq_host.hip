@@ -664,13 +664,11 @@ int lvq_consolidate(lvq_index *ix, void *stream, int64_t *n_freed_out)
         ix->lists.push_back(fresh_list);
         next = (int)ix->lists.size() - 1;
     }
-    const int nb = (int)((cap + 1023) / 1024);
-    if ((rc = dev_alloc(ix, ix->scratch, sizeof(int32_t) * (size_t)nb + 64))) return rc;
-    int32_t *counts = P<int32_t>(ix->scratch);
-    int64_t *tail = reinterpret_cast<int64_t *>(reinterpret_cast<char *>(ix->scratch.p) +
-                                                ((sizeof(int32_t) * (size_t)nb + 15) & ~(size_t)15));
-    LVQ_HIP(launch_consolidate(store_args(ix), safe, P<int32_t>(ix->stack), ix->free_top, counts, tail, s));
-    LVQ_HIP(launch_build_list(store_args(ix), P<int32_t>(ix->lists[next].buf), counts, tail + 1, s));
+    const size_t bits = consolidate_scratch(cap), tail_at = (bits + 15) & ~(size_t)15;
+    if ((rc = dev_alloc(ix, ix->scratch, tail_at + 16))) return rc;
+    int64_t *tail = reinterpret_cast<int64_t *>(reinterpret_cast<char *>(ix->scratch.p) + tail_at);
+    LVQ_HIP(launch_consolidate(store_args(ix), safe, P<int32_t>(ix->stack), ix->free_top,
+                               P<int32_t>(ix->lists[next].buf), ix->scratch.p, tail, s));
     int64_t got[2] = {0, 0};   // new stack top, list length
     LVQ_HIP(hipMemcpyAsync(got, tail, sizeof(got), hipMemcpyDeviceToHost, s));
     LVQ_HIP(hipStreamSynchronize(s));

@@ -323,12 +323,13 @@ hipError_t launch_cast16(const float *x, int64_t n, int prec, void *out, hipStre
 hipError_t launch_topk_merge(const uint64_t *part_keys, int64_t nq, int n_parts, int k, int metric,
                              int32_t *ids, float *dist, hipStream_t s);
 hipError_t launch_delete(const StoreArgs &a, const int32_t *slots, int64_t n, hipStream_t s);
-hipError_t launch_consolidate(const StoreArgs &a, uint32_t safe_epoch, int32_t *free_stack,
-                              int64_t free_top, int32_t *block_counts, int64_t *new_top,
-                              hipStream_t s);
-// The occupied slots (flags bit 0), ascending, into list; count to *len.
-hipError_t launch_build_list(const StoreArgs &a, int32_t *list, int32_t *block_counts, int64_t *len,
-                             hipStream_t s);
+// Reclaim the slots tombstoned at or before safe_epoch (pushed on the stack,
+// headers cleared) and list the occupied ones, ascending, into list; out[0]: the
+// new stack top, out[1]: the list's length.  scratch: consolidate_scratch
+// bytes, 8-byte aligned.
+size_t consolidate_scratch(int64_t capacity);
+hipError_t launch_consolidate(const StoreArgs &a, uint32_t safe_epoch, int32_t *free_stack, int64_t free_top,
+                              int32_t *list, void *scratch, int64_t *out, hipStream_t s);
 hipError_t launch_gather_rows(const StoreArgs &a, const int32_t *slots, int64_t n, uint8_t *rows_out,
                               uint8_t *resid_out, hipStream_t s);
 hipError_t launch_mean(const float *x, int64_t n, int dim, float *out, double *scratch, hipStream_t s);

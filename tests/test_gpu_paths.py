@@ -291,3 +291,36 @@ def test_split_lists_under_capture(L):
         s = torch.cuda.Stream()
     assert ix.sync() == 0
     ix.close()
+
+
+@pytest.mark.parametrize("cap", [1, 63, 64, 65, 1024, 1025, 5000])
+def test_consolidation_edges(L, cap):
+    """Consolidation over capacities around a wave, a block and several: the
+    freed slots pop in ascending order, top-k sees exactly the live rows, freed
+    headers are clear, and a second consolidation frees nothing."""
+    g = synth.rng(8100 + cap, 0)
+    d = 32
+    X = int_rows(g, max(cap, 2), d)[:cap]
+    ix = L.Index(d, 8, 0, L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=cap, means=np.zeros((1, d), np.float32))
+    used = cap - cap // 5
+    ix.insert(torch.from_numpy(X[:used]).cuda())
+    dead = np.unique(g.integers(0, used, max(1, used // 3)))
+    dead = np.unique(np.concatenate([dead, [0, used - 1]]))
+    ix.delete(torch.tensor(dead, dtype=torch.int32, device="cuda"))
+    assert ix.consolidate() == len(dead) and ix.consolidate() == 0
+    rows, _ = ix.read_rows(torch.tensor(dead, dtype=torch.int32, device="cuda"))
+    assert int(rows[:, :32].sum()) == 0
+    live = np.setdiff1d(np.arange(used), dead)
+    Q = int_queries(g, 3, d)
+    k = min(20, cap)
+    v = np.full((3, used), np.inf)
+    v[:, live] = values(False, Q, X[:used][live])
+    ids, val = best(False, v, k)
+    ids[~np.isfinite(val)] = -1
+    ti, td = ix.topk(torch.from_numpy(Q).cuda(), k)
+    np.testing.assert_array_equal(ti.cpu().numpy(), ids)
+    np.testing.assert_array_equal(td.cpu().numpy().astype(np.float64), val)
+    again = ix.insert(torch.from_numpy(X[dead]).cuda()).cpu().numpy()
+    np.testing.assert_array_equal(again, dead)
+    assert ix.sync() == 0
+    ix.close()
