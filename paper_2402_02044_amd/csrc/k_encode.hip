@@ -22,6 +22,7 @@
 // (no table lookups on the packing path).
 #pragma clang fp contract(off)
 
+#include <algorithm>
 #include <float.h>
 
 #include "lvq_internal.h"
@@ -150,6 +151,132 @@ __host__ __device__ inline int stage_stride(int d)
     return s;
 }
 
+// Nearest mean (Def. 1) of a tile of VT vectors, apart from the encoder: every
+// lane sums VR vectors x MR means at once, each sum its own serial chain over
+// the dimensions in order, with both sides staged in LDS kAssignDims at a time.
+// Bound: vector-ALU issue, the three uncontracted operations per (vector, mean,
+// dimension).  In the encoder a lane sums two means of one vector and waits for
+// each value (and lanes past the means idle), so this pays wherever the search
+// is long (see encode_assigns): 10^4 vectors of d = 768 with 16 means, encoded,
+// 83 us before and 42 us with it; 10^6 5865 and 2075 us; 10^6 of d = 96 with 256
+// means 2771 and 1597 us.  Small batches take tiles of 16 vectors, so that the
+// tiles fill the chip (10^4 x 768 x 16: 121 us with tiles of 64).
+constexpr int kAssignDims = 32;
+
+template <int VR, int MR, int ML>   // ML lanes along the means; 256 / ML along the vectors
+__global__ __launch_bounds__(256) void k_assign(const float *x, int64_t n, int dim, const float *means, int n_means,
+                                                const uint8_t *active, int32_t *out)
+{
+#pragma clang fp contract(off)
+    constexpr int VT = 256 / ML * VR, MT = ML * MR;
+    constexpr int PITCH = kAssignDims + 4;   // rows of 16-byte units, spread over the banks
+    __shared__ __align__(16) float xs[VT * PITCH];
+    __shared__ __align__(16) float ms[MT * PITCH];
+    __shared__ float bs[VT * ML];
+    __shared__ int bi[VT * ML];
+    const int tid = threadIdx.x, ml = tid % ML, vl = tid / ML;
+    const int64_t v0 = (int64_t)blockIdx.x * VT;
+    float best[VR];
+    int bm[VR];
+#pragma unroll
+    for (int i = 0; i < VR; ++i) {
+        best[i] = 0.0f;
+        bm[i] = -1;
+    }
+    for (int mb = 0; mb < n_means; mb += MT) {
+        float s[VR][MR];
+#pragma unroll
+        for (int i = 0; i < VR; ++i)
+#pragma unroll
+            for (int j = 0; j < MR; ++j) s[i][j] = 0.0f;
+        // the next chunk's values are fetched into registers while this one is summed
+        constexpr int XN = VT * kAssignDims / 256, MN = MT * kAssignDims / 256;
+        float xr[XN], mr[MN];
+        const int ld = tid % kAssignDims, lr = tid / kAssignDims;
+        constexpr int RS = 256 / kAssignDims;
+        auto fetch = [&](int d0) {
+            const int d = d0 + ld;
+#pragma unroll
+            for (int e = 0; e < XN; ++e) {
+                const int64_t v = v0 + lr + RS * e;
+                xr[e] = d < dim && v < n ? x[v * dim + d] : 0.0f;
+            }
+#pragma unroll
+            for (int e = 0; e < MN; ++e) {
+                const int m = mb + lr + RS * e;
+                mr[e] = d < dim && m < n_means ? means[(int64_t)m * dim + d] : 0.0f;
+            }
+        };
+        fetch(0);
+        for (int d0 = 0; d0 < dim; d0 += kAssignDims) {
+            const int dn = min(kAssignDims, dim - d0);
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < XN; ++e) xs[(lr + RS * e) * PITCH + ld] = xr[e];
+#pragma unroll
+            for (int e = 0; e < MN; ++e) ms[(lr + RS * e) * PITCH + ld] = mr[e];
+            __syncthreads();
+            if (d0 + kAssignDims < dim) fetch(d0 + kAssignDims);
+            // (positions past the last dimension add 0 * 0, which changes no sum)
+#pragma unroll 2
+            for (int d = 0; d < kAssignDims; d += 4) {
+                if (d >= dn) break;
+                float4 xv[VR], mv[MR];
+#pragma unroll
+                for (int i = 0; i < VR; ++i) xv[i] = *reinterpret_cast<const float4 *>(xs + (vl * VR + i) * PITCH + d);
+#pragma unroll
+                for (int j = 0; j < MR; ++j) mv[j] = *reinterpret_cast<const float4 *>(ms + (ml + ML * j) * PITCH + d);
+#pragma unroll
+                for (int i = 0; i < VR; ++i)
+#pragma unroll
+                    for (int j = 0; j < MR; ++j) {
+                        auto step = [&](float a, float b) {
+                            float e = a - b;
+                            e = e * e;
+                            s[i][j] = s[i][j] + e;
+                        };
+                        step(xv[i].x, mv[j].x);
+                        step(xv[i].y, mv[j].y);
+                        step(xv[i].z, mv[j].z);
+                        step(xv[i].w, mv[j].w);
+                    }
+            }
+        }
+        // a lane's means ascend: ties keep the lower one; retired ones are never chosen
+#pragma unroll
+        for (int j = 0; j < MR; ++j) {
+            const int m = mb + ml + ML * j;
+            const bool ok = m < n_means && active[m] != 0;
+#pragma unroll
+            for (int i = 0; i < VR; ++i)
+                if (ok && (bm[i] < 0 || s[i][j] < best[i])) {
+                    best[i] = s[i][j];
+                    bm[i] = m;
+                }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < VR; ++i) {
+        bs[(vl * VR + i) * ML + ml] = best[i];
+        bi[(vl * VR + i) * ML + ml] = bm[i];
+    }
+    __syncthreads();
+    for (int v = tid; v < VT; v += 256) {
+        if (v0 + v >= n) continue;
+        float b = 0.0f;
+        int m = -1;
+        for (int l = 0; l < ML; ++l) {
+            const float ob = bs[v * ML + l];
+            const int om = bi[v * ML + l];
+            if (om >= 0 && (m < 0 || ob < b || (ob == b && om < m))) {
+                b = ob;
+                m = om;
+            }
+        }
+        out[v0 + v] = m < 0 ? 0 : m;
+    }
+}
+
 template <int B1, int B2, int G>
 __global__ __launch_bounds__(256) void k_encode(EncodeArgs a)
 {
@@ -211,7 +338,9 @@ __global__ __launch_bounds__(256) void k_encode(EncodeArgs a)
 
     // Def. 1: nearest mean, sequential binary32 sum per mean, ties to lower m
     int mstar = 0;
-    if (M > 1 && active && finite) {
+    if (a.assigned) {
+        if (active && finite) mstar = a.assigned[i];
+    } else if (M > 1 && active && finite) {
         float best = 0.0f;
         int bm = -1;
         // two means per pass (m0 and m0 + G), each summed in dimension order
@@ -453,9 +582,49 @@ static hipError_t launch_encode_t(const EncodeArgs &a, int G, size_t lds, int64_
     return hipGetLastError();
 }
 
-hipError_t launch_encode(const EncodeArgs &a, hipStream_t s)
+// The encoder's own search is as fast on short vectors (dim 128, 2x10^5 of them:
+// 16 means 67 us there, 67 here; 32 means 112 and 108; 64 x 65 104 and 151) and
+// on few of them, where one launch less counts (dim 160, 2x10^4: 19 and 22; 1000
+// of dim 768: 36 and 36, 2048: 37 and 30).  From 192 dimensions the search here wins with any
+// number of means (dim 200, 2x10^5, 16: 170 and 136; dim 333: 658 and 299; dim 768
+// with 2: 1073 and 495), below them with many (96 x 128 means: 349 and 217).
+bool encode_assigns(int64_t n, int dim, int n_means)
 {
+    return n_means > 1 && n >= 2048 && (dim >= 192 || (n_means >= 96 && dim >= 64));
+}
+
+static hipError_t launch_assign(const EncodeArgs &a, int32_t *out, hipStream_t s)
+{
+    auto run = [&](auto kern, int vt) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)((a.n + vt - 1) / vt)), dim3(256), 0, s, a.x, a.n, a.f.dim, a.means,
+                           a.n_means, a.mean_active, out);
+        return hipGetLastError();
+    };
+    // (lanes past the last mean work for nothing: a tile is as wide as the means need)
+    const int mr = std::min(4, (a.n_means + 15) / 16);
+    if (a.n < 32768) {
+        if (mr == 1) return run(k_assign<1, 1, 16>, 16);
+        if (mr == 2) return run(k_assign<1, 2, 16>, 16);
+        if (mr == 3) return run(k_assign<1, 3, 16>, 16);
+        return run(k_assign<1, 4, 16>, 16);
+    }
+    if (mr == 1) return run(k_assign<4, 1, 16>, 64);
+    if (mr == 2) return run(k_assign<4, 2, 16>, 64);
+    if (mr == 3) return run(k_assign<4, 3, 16>, 64);
+    return run(k_assign<4, 4, 16>, 64);
+}
+
+hipError_t launch_encode(const EncodeArgs &args, int32_t *assign_buf, hipStream_t s)
+{
+    EncodeArgs a = args;
     if (a.n <= 0) return hipSuccess;
+    a.assigned = nullptr;
+    if (assign_buf) {
+        const hipError_t e = launch_assign(a, assign_buf, s);
+        if (e != hipSuccess) return e;
+        a.assigned = assign_buf;
+        a.means_lds = 0;
+    }
     // lanes per vector: the fewest (8..64) giving each lane at most four
     // packing units
     const int U = (a.f.bits1 == 4 || a.f.bits2 == 4) ? 8 : 4;

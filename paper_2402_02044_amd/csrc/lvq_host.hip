@@ -160,7 +160,7 @@ void pin_after_capture(lvq_index *ix, hipStream_t s, bool reads_list)
     if (!ix->capturing) return;
     Workspace &w = ix->ws[s];
     for (DevBuf *b : {&w.qk, &w.qsum, &w.cm, &w.order, &w.queue, &w.part, &w.q16, &w.gthr, &w.mkeys, &w.members, &w.moffs,
-                      &w.mcount, &w.mcursor, &w.probe, &w.qoffs, &w.qids})
+                      &w.mcount, &w.mcursor, &w.probe, &w.qoffs, &w.qids, &w.assign})
         if (b->p) b->pinned = true;
     if (reads_list && ix->list_active >= 0) ix->lists[ix->list_active].captured = true;
 }
@@ -489,7 +489,7 @@ int lvq_destroy(lvq_index *ix)
     for (auto &kv : ix->ws) {
         Workspace &w = kv.second;
         for (DevBuf *b : {&w.qk, &w.qsum, &w.cm, &w.order, &w.queue, &w.part, &w.q16, &w.gthr, &w.mkeys, &w.members, &w.moffs,
-                          &w.mcount, &w.mcursor, &w.probe, &w.qoffs, &w.qids})
+                          &w.mcount, &w.mcursor, &w.probe, &w.qoffs, &w.qids, &w.assign})
             dev_free(ix, *b);
     }
     for (DevBuf *b : {&ix->means, &ix->means_t, &ix->muk, &ix->kmask, &ix->kdim, &ix->rows,
@@ -546,6 +546,8 @@ int lvq_set_means(lvq_index *ix, const float *means_host, int32_t n_means, int32
     return LVQ_OK;
 }
 
+constexpr int64_t kAssignRun = 1 << 20;   // vectors per pass of the nearest-mean kernel
+
 static int encode_common(lvq_index *ix, const float *x, int64_t n, uint8_t *rows, uint8_t *resid,
                          const uint64_t *ext, int32_t *slots_out, bool store, hipStream_t s)
 {
@@ -568,7 +570,42 @@ static int encode_common(lvq_index *ix, const float *x, int64_t n, uint8_t *rows
     a.ext_ids = ext;
     a.epoch = ix->epoch;
     a.err = P<uint32_t>(ix->err);
-    LVQ_HIP(launch_encode(a, s));
+    // Several means: found in a kernel of its own where that pays and there is
+    // room for the ids (this stream's own buffer; in a captured call or under a
+    // memory budget, which it would take from the queries, the encoder searches).
+    int32_t *buf = nullptr;
+    if (encode_assigns(n, ix->f.dim, ix->n_means)) {
+        int rc = begin_call(ix, s);
+        if (rc) return rc;
+        if (!ix->capturing && ix->cfg.mem_budget_bytes <= 0) {
+            Workspace &w = workspace(ix, s);
+            size_t room = 4096;   // (doubled, so that growing batches seldom grow the buffer)
+            while ((int64_t)room < std::min<int64_t>(n, kAssignRun)) room *= 2;
+            if (dev_alloc(ix, w.assign, sizeof(int32_t) * room) == LVQ_OK)
+                buf = P<int32_t>(w.assign);
+            else
+                (void)hipGetLastError();   // the call goes on without it
+        }
+    }
+    if (!buf) {
+        LVQ_HIP(launch_encode(a, nullptr, s));
+        return LVQ_OK;
+    }
+    for (int64_t at = 0; at < n; at += kAssignRun) {
+        EncodeArgs p = a;
+        p.n = std::min<int64_t>(n - at, kAssignRun);
+        p.x = x + at * ix->f.dim;
+        if (store) {
+            p.free_top = a.free_top - at;
+            p.list_out = a.list_out + at;
+            p.slots_out = slots_out + at;
+            if (ext) p.ext_ids = ext + at;
+        } else {
+            p.rows = rows + at * ix->f.row_bytes;
+            if (resid) p.resid = resid + at * ix->f.resid_bytes;
+        }
+        LVQ_HIP(launch_encode(p, buf, s));
+    }
     return LVQ_OK;
 }
 

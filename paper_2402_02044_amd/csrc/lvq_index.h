@@ -37,6 +37,7 @@ struct Workspace {
     // soft inverted index: this stream's per-mean member lists (built at
     // store version members_version) and per-call routing / candidate lists
     DevBuf members, moffs, mcount, mcursor, probe, qoffs, qids;
+    DevBuf assign;   // encoder: nearest means of one pass
     uint64_t members_version = ~0ull;
 };
 

@@ -48,6 +48,7 @@ struct EncodeArgs {
     int n_means;
     int means_lds;           // stage the means in LDS (small M x dim)
     const uint8_t *mean_active;  // n_means flags: 0 = retired (not chosen by the nearest-mean search)
+    const int32_t *assigned;     // n mean ids found beforehand, or NULL: searched by the encoder
     Format f;
     uint8_t *rows;           // output rows (row i at rows + slot(i) * row_bytes)
     uint8_t *resid;
@@ -144,7 +145,10 @@ struct StoreArgs {
 
 // ---- launchers (each returns hipSuccess or the launch error) --------------
 
-hipError_t launch_encode(const EncodeArgs &a, hipStream_t s);
+// (assign_buf: n int32 to find the means into first, or NULL)
+hipError_t launch_encode(const EncodeArgs &a, int32_t *assign_buf, hipStream_t s);
+// Whether finding the means in a kernel of its own pays.
+bool encode_assigns(int64_t n, int dim, int n_means);
 hipError_t launch_prep(const PrepArgs &a, hipStream_t s);
 // The vector scan's queries: tiles of tq queries as [position][query] (L2:
 // less the mean muk; zero past nq) into a.qk, a.qsum and a.cm as launch_prep

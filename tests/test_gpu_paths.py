@@ -324,3 +324,71 @@ def test_consolidation_edges(L, cap):
     np.testing.assert_array_equal(again, dead)
     assert ix.sync() == 0
     ix.close()
+
+
+@pytest.mark.parametrize("d,M,n", [
+    (192, 2, 2048), (200, 15, 2049), (333, 16, 2070), (194, 17, 2100), (768, 33, 2111), (205, 49, 4097),
+    (97, 96, 2300), (64, 256, 3001),                # tiles of 16 vectors, every width in means
+    (192, 16, 32768), (193, 20, 32769), (224, 40, 32831), (100, 100, 40001)])   # tiles of 64
+def test_means_found_apart_match_the_encoder_search(L, d, M, n):
+    """Large batches' nearest means come from a kernel of their own, small
+    batches' from the encoder: rows and residuals are the same bytes, with
+    repeated means (ties), retired ones, vectors that hold inf or NaN and ones
+    whose sums overflow; so are the rows of an insert (and its slots), of a
+    captured call and of an index with a memory budget."""
+    g = synth.rng(8200 + d + M, 0)
+    mu = g.standard_normal((M, d)).astype(np.float32)
+    mu[M - 1] = mu[0]                                # a tie for every vector near it
+    X = (mu[g.integers(0, M, n)] + 0.5 * g.standard_normal((n, d))).astype(np.float32)
+    X[1, d // 2], X[n - 1, 0], X[n // 2, d - 1] = np.inf, np.nan, -np.inf
+    X[2], X[n - 2] = 3e38, -3e38
+    x = torch.from_numpy(X).cuda()
+    made = [L.Index(d, 8, 8, L.LVQ_L2, L.LVQ_SEQUENTIAL, means=mu, capacity=n, mem_budget_bytes=b) for b in (0, 1 << 32)]
+    ix = made[0]
+    if M > 4:
+        for i in made:
+            i.retire_means([1, M - 2])
+    want = [torch.cat(t) for t in zip(*[ix.encode(x[a:a + 1024]) for a in range(0, n, 1024)])]
+    got = ix.encode(x)
+    for i in made:
+        got = i.encode(x)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ix.encode(x)
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        got = ix.encode(x)
+    for _ in range(3):
+        for t in got:
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    slots = ix.insert(x, ext_ids=torch.arange(n, device="cuda") + 7)
+    assert torch.equal(slots.sort().values, torch.arange(n, dtype=torch.int32, device="cuda"))
+    rows, resid = ix.read_rows(slots)
+    assert torch.equal(rows[:, 32:], want[0][:, 32:]) and torch.equal(resid, want[1])
+    assert torch.equal(rows[:, :12], want[0][:, :12])       # delta, lower bound, mean
+    for i in made:
+        i.sync()
+        i.close()
+
+
+def test_encode_runs_past_one_pass_of_means(L):
+    """More vectors than one pass of the nearest-mean kernel takes: the rows and
+    slots after the first pass are the right ones."""
+    n, d, M = (1 << 20) + 77, 192, 3
+    g = synth.rng(8300, 0)
+    mu = (10 * g.standard_normal((M, d))).astype(np.float32)
+    base = torch.from_numpy((mu[g.integers(0, M, 1024)] + g.standard_normal((1024, d))).astype(np.float32)).cuda()
+    ix = L.Index(d, 4, 0, L.LVQ_L2, L.LVQ_SEQUENTIAL, means=mu, capacity=n)
+    x = base.repeat((n + 1023) // 1024, 1)[:n].contiguous()
+    want = ix.encode(base)[0].repeat((n + 1023) // 1024, 1)[:n]
+    assert torch.equal(ix.encode(x)[0], want)
+    slots = ix.insert(x)
+    pick = torch.cat([torch.arange(5), torch.arange((1 << 20) - 5, n)]).cuda()
+    assert torch.equal(ix.read_rows(slots[pick].contiguous())[0][:, 32:], want[pick][:, 32:])
+    assert ix.sync() == 0
+    ix.close()
