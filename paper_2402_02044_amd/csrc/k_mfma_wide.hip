@@ -50,7 +50,52 @@ size_t wide_lds(int qb, int kpos, int rb, int prec, int bits2, int n_means)
     return wide_lds_bytes(qb, kpos, rb, prec == LVQ_FP32 ? 4 : 2, mm ? n_means : 0, 12 + (mm ? 4 : 0) + (ch2 ? 4 : 0));
 }
 
+// One wave per query: the k-th largest of its 64 * E sampled maxima becomes
+// its shared bound, by a binary search over the order keys (smaller is better).
+template <int E>
+__global__ __launch_bounds__(256) void k_sample_bound(const float *gmax, int groups, int64_t nq, int k, uint32_t *gthr)
+{
+    const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (q >= nq) return;
+    uint32_t key[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int g = 64 * e + lane;
+        const float v = g < groups ? gmax[q * groups + g] : -__builtin_inff();
+        key[e] = (uint32_t)(make_key(v, 0, LVQ_IP) >> 32);
+    }
+    uint32_t t = 0;   // the largest t with fewer than k keys below it
+    for (int bit = 31; bit >= 0; --bit) {
+        const uint32_t c = t | (1u << bit);
+        int below = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) below += __builtin_popcountll(__ballot(key[e] < c));
+        if (below < k) t = c;
+    }
+    // (fewer than k rows scored in the sample: no bound)
+    if (lane == 0 && t < (uint32_t)(make_key(-__builtin_inff(), 0, LVQ_IP) >> 32)) gthr[q] = t;
+}
+
 }  // namespace
+
+int mfma_wide_round(int bits1, int bits2, int kpos, int prec)
+{
+    int qb = 0, rb = 0;
+    return wide_kernel(bits1, bits2, kpos, prec, &qb, &rb) ? wide_waves(rb) * 32 * rb : 0;
+}
+
+hipError_t launch_sample_bound(const float *gmax, int groups, int64_t nq, int k, uint32_t *gthr, hipStream_t s)
+{
+    if (groups < k || groups > 64 * 32 || k < 1) return hipErrorInvalidValue;
+    auto run = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, gmax, groups, nq, k, gthr);
+        return hipGetLastError();
+    };
+    if (groups <= 256) return run(k_sample_bound<4>);
+    if (groups <= 1024) return run(k_sample_bound<16>);
+    return run(k_sample_bound<32>);
+}
 
 int mfma_wide_query_block(int bits1, int bits2, int kpos, int prec, int k, int n_means, size_t lds_max)
 {

@@ -42,6 +42,12 @@
 // the same rows through its L2.  The both-level forms also read each row's
 // residual codes through the ring (the decoded FP32 form its header a round
 // ahead).
+//
+// Sample pass (gmax set): the same products and scores over the first
+// sample_rows rows of every part, of which each wave keeps its largest score
+// per query -- no keys, no merges.  The k-th largest of a query's maxima (over
+// different rows) is a score that k rows reach, computed by the same
+// operations, so gthr starts there and the answers are the same.
 #pragma once
 
 #include <type_traits>
@@ -145,7 +151,7 @@ __global__ __launch_bounds__(64 * wide_waves(RB), 1) void k_scan_mfma_wide(ScanA
         const int64_t q0 = qt * TQ;
         const int nqt = (int)min<int64_t>(TQ, a.nq - q0);
         const int64_t r0 = (int64_t)part * a.rows_per_part;
-        const int64_t r1 = min<int64_t>(a.n_rows, r0 + a.rows_per_part);
+        const int64_t r1 = min<int64_t>(a.n_rows, r0 + (a.gmax ? a.sample_rows : a.rows_per_part));
         auto out_keys = [&](int qi) { return a.part_keys + ((q0 + qi) * a.n_parts + part) * (int64_t)k; };
 
         __syncthreads();   // the previous tile is done with LDS
@@ -164,7 +170,7 @@ __global__ __launch_bounds__(64 * wide_waves(RB), 1) void k_scan_mfma_wide(ScanA
                 cmt[t] = qi < nqt ? a.cm[(q0 + qi) * a.n_means + m] : 0.0f;
             }
         }
-        for (int t = tid; t < TQ * ks; t += 64 * WAVES) region[(size_t)(t / ks) * cap + t % ks] = kNoKey;
+        for (int t = tid; !a.gmax && t < TQ * ks; t += 64 * WAVES) region[(size_t)(t / ks) * cap + t % ks] = kNoKey;
         float qs[QB], cq[QB], tau[QB];
 #pragma unroll
         for (int b = 0; b < QB; ++b) {
@@ -177,7 +183,8 @@ __global__ __launch_bounds__(64 * wide_waves(RB), 1) void k_scan_mfma_wide(ScanA
         __syncthreads();
 
         if (r0 >= r1) {
-            // an empty part contributes no keys
+            // an empty part contributes no keys (a sample has none: its parts
+            // start below n_rows)
             for (int qi = wave; qi < nqt; qi += WAVES)
                 for (int i = lane; i < k; i += 64) out_keys(qi)[i] = kNoKey;
             continue;
@@ -358,7 +365,7 @@ __global__ __launch_bounds__(64 * wide_waves(RB), 1) void k_scan_mfma_wide(ScanA
 #pragma unroll
             for (int b = 0; b < QB; ++b) tf[b] = thr_f[32 * b + col];
 #pragma unroll
-            for (int b = 0; b < QB; ++b) {
+            for (int b = 0; b < QB && !a.gmax; ++b) {
                 const float other = key_score((uint64_t)gb[b] << 32, LVQ_IP);
                 tau[b] = fmaxf(tau[b], fmaxf(tf[b], gb[b] != 0xFFFFFFFFu ? other : -__builtin_inff()));
             }
@@ -407,6 +414,29 @@ __global__ __launch_bounds__(64 * wide_waves(RB), 1) void k_scan_mfma_wide(ScanA
                         if constexpr (CH2) return fmaf(d2, acc2[j][b][i], t);
                         else return t;
                     };
+                    if (a.gmax) {
+                        // sample pass: tau is the lane's largest score
+                        // (a NaN score leaves it)
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            const int m0 = 32 * j + 8 * g + 4 * half;
+                            const float4 L = *reinterpret_cast<const float4 *>(wl + m0);
+                            const float4 D = *reinterpret_cast<const float4 *>(wd + m0);
+                            int4 M4 = make_int4(0, 0, 0, 0);
+                            if constexpr (TAB) M4 = *reinterpret_cast<const int4 *>(wm + m0);
+                            float4 D2 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                            if constexpr (CH2) D2 = *reinterpret_cast<const float4 *>(wd2 + m0);
+                            const float lr[4] = {L.x, L.y, L.z, L.w}, dr[4] = {D.x, D.y, D.z, D.w};
+                            const float d2r[4] = {D2.x, D2.y, D2.z, D2.w};
+                            const int mr[4] = {M4.x, M4.y, M4.z, M4.w};
+#pragma unroll
+                            for (int b = 0; b < QB; ++b)
+#pragma unroll
+                                for (int r4 = 0; r4 < 4; ++r4)
+                                    tau[b] = fmaxf(tau[b], score(b, 4 * g + r4, lr[r4], dr[r4], d2r[r4], mr[r4]));
+                        }
+                        continue;
+                    }
                     if constexpr (CH2) {
                         // One sweep: each score that reaches its bound is
                         // appended at once.  A score here costs three
@@ -548,7 +578,7 @@ __global__ __launch_bounds__(64 * wide_waves(RB), 1) void k_scan_mfma_wide(ScanA
 #pragma unroll
             for (int t = 0; t < NQW; ++t) {
                 const int qw = 64 * t, qi_l = qw + lane;
-                uint64_t m = __ballot(qi_l < nqt && qi_l % WAVES == wave && (last || cv[t] >= kWideMerge));
+                uint64_t m = __ballot(!a.gmax && qi_l < nqt && qi_l % WAVES == wave && (last || cv[t] >= kWideMerge));
                 while (m) {
                     const int qi = qw + __builtin_ctzll(m);
                     m &= m - 1;
@@ -578,6 +608,15 @@ __global__ __launch_bounds__(64 * wide_waves(RB), 1) void k_scan_mfma_wide(ScanA
                     hd[j] = hn[j];
                     ep[j] = en[j];
                 }
+            }
+        }
+        if (a.gmax) {
+            // one value per wave and query, over both halves' rows
+#pragma unroll
+            for (int b = 0; b < QB; ++b) {
+                const float o = fmaxf(tau[b], __shfl_xor(tau[b], 32, 64));
+                if (half == 0 && 32 * b + col < nqt)
+                    a.gmax[((q0 + 32 * b + col) * a.n_parts + part) * WAVES + wave] = o;
             }
         }
     }

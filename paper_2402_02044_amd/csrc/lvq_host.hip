@@ -1118,23 +1118,74 @@ static int64_t scan_parts_mfma(const lvq_index *ix, int64_t qtiles, int32_t k, i
     return parts;
 }
 
+// Sample pass of the wide MFMA scan: `parts` stretches of `rows` rows, spread
+// over the list, are scored first and only each wave's largest score per query
+// is kept; the k-th largest of these 8 * parts maxima is a bound that k rows
+// reach, so the scan proper starts with it instead of with none.
+//
+// A scan without it keeps every score of a part's first round and about
+// k ln(rows) more per part and query, at the price of sorts and of LDS atomics;
+// with it N k / S scores pass for a sample of S rows, so S goes with
+// sqrt(N k / price of a row).  10^6 x 768 4x8 (16 means) at both levels, k = 10,
+// 300 queries: 1658 us without, 1398 / 1331 / 1317 / 1271 / 1322 with S = 4k / 8k / 16k /
+// 33k / 66k; 64 queries 1843 and 425; 10^6 x 512 first level: 16 queries 587 and 230,
+// 1000 queries 1686 and 1190; 4096 x 2x10^6, k = 100: 10,448 and 9035; 10^6 x 96, 300
+// queries 1123 and 245; FP32, 10^6 x 512, 100 queries 1915 and 1170.  The maxima of
+// fewer than 4 k groups miss much of the top k (3x10^5 x 768 both levels, k = 500: 512
+// groups 3388 us, 2048 1623, none 4104).
+struct ScanSample {
+    int64_t parts, rows;   // parts = 0: no sample
+};
+
+static ScanSample scan_sample(const lvq_index *ix, int64_t qtiles, int32_t k, int64_t n_rows, int bits2, int32_t prec)
+{
+    const Format &f = ix->f;
+    const int64_t round = mfma_wide_round(f.bits1, bits2, f.kpos, prec);
+    const bool f32 = prec == LVQ_FP32;
+    const double row_cost = f32 ? 8.0 : 1.0;
+    const double want = std::sqrt(80.0 * 512.0 / (f.kpos * row_cost) * (double)n_rows * k);
+    const int64_t most = n_rows / (2 * round);   // at most half the rows
+    const int64_t slots = std::max<int64_t>(8, ix->n_cu / 8 * 8);
+    // (a pass that leaves half the chip idle costs no more with larger samples)
+    const int64_t rounds =
+        std::min<int64_t>(most, std::max<int64_t>((int64_t)(want / round) + 1, slots / (2 * qtiles)));
+    const int64_t least = std::min<int64_t>({most, 256, std::max<int64_t>(2, (k + 1) / 2)});
+    // a tile's queries are staged once: up to four rounds each where the tiles
+    // fill the chip anyway
+    int64_t per = 1;
+    while (per < 4 && rounds >= 2 * per * least && qtiles * ((rounds + per - 1) / per) > 2 * slots) per *= 2;
+    while (per < 8 && (rounds + per - 1) / per > 256) per *= 2;
+    int64_t parts = std::min<int64_t>(256, std::max(least, (rounds + per - 1) / per));
+    // whole waves of workgroups, where there is more than one
+    if (qtiles * parts > slots && slots / qtiles >= least) {
+        const int64_t waves = std::max<int64_t>(1, (qtiles * parts + slots / 2) / slots);
+        parts = std::min<int64_t>(256, std::max(least, waves * slots / qtiles));
+    }
+    if (parts < 1 || 8 * parts < k || parts * per * round > n_rows) return {0, 0};
+    return {parts, per * round};
+}
+
 // Row parts and persistent grid of the wide MFMA scan (one workgroup per
 // compute unit, a multiple of 8 for the XCD-aware tile walk).  Time model:
 // each workgroup runs ceil(tiles per XCD / workgroups per XCD) tiles of
-// N = n_rows / parts rows, plus a per-tile cost in 16-bit row equivalents:
-// 10,240 for staging the queries and the final merge, and the appends of a
-// part's loose bound.  A 32 x 32 block of scores holds a key beating the
-// running k-th best of t rows with probability about min(1, 1024 k / t), so
-// the blocks that append add about 512 k (1 + ln(N / 1024 k)) rows' worth.
+// R = n_rows / parts rows, plus a per-tile cost in 16-bit row equivalents: 2200
+// for staging the queries and the final merge (10^5 x 512, 1000 queries: 8 x 32
+// tiles 199 us, 8 x 64 251; 10^6 x 96, 300 queries: 3 x 64 tiles 271, 3 x 256 278) and
+// 16 for each key that passes: R k / S per query while R is less than the S sampled rows,
+// k (1 + ln(R / S)) beyond.  Without a sample a part's bound starts loose: a 32 x 32
+// block of scores holds a key beating the running k-th best of t rows with
+// probability about min(1, 1024 k / t), so the blocks that append add about
+// 512 k (1 + ln(R / 1024 k)) rows' worth, and 10,240 for the rest.
 // An FP32 row costs about 8 16-bit ones (a sixteenth of the matrix-core
-// rate, half the queries per tile).  Parts keep at least 8 rounds of rows,
-// and the merge (parts * k keys, + k) fits one workgroup's LDS.
+// rate, half the queries per tile).  Parts keep at least 512 rows (4096 without a
+// sample), and the merge (parts * k keys, + k) fits one workgroup's LDS.
 static int64_t scan_parts_wide(const lvq_index *ix, int64_t qtiles, int32_t k, int64_t n_rows, int32_t prec,
-                               int64_t *grid)
+                               const ScanSample &sm, int64_t *grid)
 {
     const int64_t slots = std::max<int64_t>(8, ix->n_cu / 8 * 8);
     const int64_t max_parts = std::max<int64_t>(
-        1, std::min<int64_t>(n_rows / 4096, (int64_t)(ix->lds_max / 8 - k) / k));
+        1, std::min<int64_t>(n_rows / (sm.parts ? 512 : 4096), (int64_t)(ix->lds_max / 8 - k) / k));
+    const double sampled = (double)std::max<int64_t>(1, sm.parts * sm.rows);
     int64_t parts = 1;
     double best = 0.0;
     for (int64_t p = 1; p <= max_parts; ++p) {
@@ -1144,7 +1195,9 @@ static int64_t scan_parts_wide(const lvq_index *ix, int64_t qtiles, int32_t k, i
         const int64_t iters = (per_xcd + g / 8 - 1) / (g / 8);
         const double rows = (double)((n_rows + p - 1) / p), warm = 1024.0 * k;
         const double row_cost = prec == LVQ_FP32 ? 8.0 : 1.0;
-        const double cost = (double)iters * (rows + (10240.0 + 0.5 * warm * (1.0 + std::log(std::max(1.0, rows / warm)))) / row_cost);
+        const double extra = sm.parts ? 2200.0 + 16.0 * k * (rows < sampled ? rows / sampled : 1.0 + std::log(rows / sampled))
+                                      : 10240.0 + 0.5 * warm * (1.0 + std::log(std::max(1.0, rows / warm)));
+        const double cost = (double)iters * (rows + extra / row_cost);
         if (p == 1 || cost < best) {
             best = cost;
             parts = p;
@@ -1223,6 +1276,8 @@ int lvq::host_topk(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq, i
     a.part_keys = P<uint64_t>(w.part);
     a.err = P<uint32_t>(ix->err);
     a.mks = scan_sorted_keys(k);
+    a.gmax = nullptr;
+    a.sample_rows = 0;
     ix->last_wg = qtiles * parts;
     ix->last_lists = 0;
     ix->last_parts = (int32_t)parts;
@@ -1283,12 +1338,30 @@ static int topk_mfma(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq,
     LVQ_HIP(launch_prep_scan(q_dev, nq, f.dim, f.kpos, f.bits1, qb, prec, P<int32_t>(ix->kdim), P<float>(ix->means),
                              ix->n_means, w.q16.p, P<float>(w.qsum), P<float>(w.cm), P<uint32_t>(w.gthr), s));
     const int64_t n_rows = ix->list_len;
+    // Under a memory budget the scan is sized as without a sample, and where the
+    // buffers have no room (a captured call), in fewer parts and without one.
+    ScanSample sm = {0, 0};
+    if (qbw && ix->cfg.mem_budget_bytes <= 0) sm = scan_sample(ix, qtiles, k, n_rows, bits2, prec);
     int64_t grid = 0;
-    const int64_t parts =
-        qbw ? scan_parts_wide(ix, qtiles, k, n_rows, prec, &grid) : scan_parts_mfma(ix, qtiles, k, n_rows);
+    int64_t parts = qbw ? scan_parts_wide(ix, qtiles, k, n_rows, prec, sm, &grid) : scan_parts_mfma(ix, qtiles, k, n_rows);
+    for (;;) {
+        const size_t keys = sizeof(uint64_t) * (size_t)nq * parts * k;
+        rc = dev_alloc(ix, w.part, std::max(keys, sizeof(float) * 8 * (size_t)nq * sm.parts));
+        if (rc == LVQ_OK && qbw) rc = dev_alloc(ix, w.mkeys, sizeof(uint64_t) * (size_t)grid * tq * mfma_wide_cap(k));
+        if (rc == LVQ_OK) break;
+        if (!sm.parts && parts == 1) return rc;
+        (void)hipGetLastError();
+        if (sm.parts) {
+            sm = {0, 0};
+            if (qbw) parts = scan_parts_wide(ix, qtiles, k, n_rows, prec, sm, &grid);
+        } else if (qbw) {
+            parts /= 2;
+            grid = std::min<int64_t>(grid, (qtiles * parts + 7) / 8 * 8);
+        } else {
+            return rc;
+        }
+    }
     const int64_t rows_per_part = std::max<int64_t>(1, (n_rows + parts - 1) / parts);
-    if ((rc = dev_alloc(ix, w.part, sizeof(uint64_t) * (size_t)nq * parts * k))) return rc;
-    if (qbw && (rc = dev_alloc(ix, w.mkeys, sizeof(uint64_t) * (size_t)grid * tq * mfma_wide_cap(k)))) return rc;
     ScanArgs a;
     a.rows = P<uint8_t>(ix->rows);
     a.resid = P<uint8_t>(ix->resid);
@@ -1317,10 +1390,22 @@ static int topk_mfma(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq,
     a.mkeys = qbw ? P<uint64_t>(w.mkeys) : nullptr;
     a.mcap = qbw ? mfma_wide_cap(k) : 0;
     a.mks = qbw ? mfma_wide_sorted(k) : 0;
+    a.gmax = nullptr;
+    a.sample_rows = 0;
     ix->last_wg = qbw ? grid : (qtiles * parts + 7) / 8 * 8;
     ix->last_lists = 0;
     ix->last_parts = (int32_t)parts;
     if ((rc = timing_begin(ix, s))) return rc;
+    if (sm.parts) {
+        ScanArgs b = a;
+        b.gmax = P<float>(w.part);   // (the scan proper overwrites it)
+        b.sample_rows = sm.rows;
+        b.rows_per_part = n_rows / sm.parts;
+        b.n_parts = (int)sm.parts;
+        const int64_t g = std::min<int64_t>(std::max<int64_t>(8, ix->n_cu / 8 * 8), (qtiles * sm.parts + 7) / 8 * 8);
+        LVQ_HIP(launch_scan_mfma_wide(b, f.bits1, bits2, prec, g, ix->lds_max, s));
+        LVQ_HIP(launch_sample_bound(b.gmax, (int)sm.parts * 8, nq, k, a.gthr, s));
+    }
     if (qbw)
         LVQ_HIP(launch_scan_mfma_wide(a, f.bits1, bits2, prec, grid, ix->lds_max, s));
     else
@@ -1598,6 +1683,24 @@ int lvq::host_reserve(lvq_index *ix, hipStream_t s, int64_t max_nq, int32_t k_fi
     const size_t qsum = sizeof(float) * (size_t)max_nq;
     const size_t cm = sizeof(float) * (size_t)max_nq * kMaxMeans;   // any mean count the index may reach
     if (prec == LVQ_FP32 || k_rerank > 0) qk = sizeof(float) * (size_t)((max_nq + 15) / 16 * 16) * f.kpos;
+    // the wide matrix-core scan, at the most queries of every tile count; with
+    // a sample its part count does not only grow with the rows, so fewer are
+    // looked at too
+    auto reserve_wide = [&](int64_t tq, int bits2) {
+        for (int64_t rows = n_rows;; rows = rows * 7 / 8) {
+            for (int64_t qtiles = 1; (qtiles - 1) * tq < max_nq; ++qtiles) {
+                const int64_t nq = std::min<int64_t>(max_nq, qtiles * tq);
+                int64_t grid = 0;
+                ScanSample sm = {0, 0};
+                if (ix->cfg.mem_budget_bytes <= 0) sm = scan_sample(ix, qtiles, k_first, rows, bits2, prec);
+                const int64_t parts = scan_parts_wide(ix, qtiles, k_first, rows, prec, sm, &grid);
+                part = std::max(part, sizeof(uint64_t) * (size_t)(nq * parts * k_first));
+                part = std::max(part, sizeof(float) * 8 * (size_t)(nq * sm.parts));
+                mkeys = std::max(mkeys, sizeof(uint64_t) * (size_t)grid * tq * mfma_wide_cap(k_first));
+            }
+            if (rows <= 512 || ix->cfg.mem_budget_bytes > 0) break;
+        }
+    };
     if (prec == LVQ_FP32) {
         gthr = sizeof(uint32_t) * (size_t)max_nq;
         // (the vector scan's tile size changes once with the batch size)
@@ -1620,12 +1723,7 @@ int lvq::host_reserve(lvq_index *ix, hipStream_t s, int64_t max_nq, int32_t k_fi
         if (qbf) {
             const int64_t tq = 32 * qbf;
             q16 = (size_t)((max_nq + tq - 1) / tq) * tq * f.kpos * 4;
-            for (int64_t nq = 1; nq <= max_nq; ++nq) {
-                int64_t grid = 0;
-                const int64_t parts = scan_parts_wide(ix, (nq + tq - 1) / tq, k_first, n_rows, LVQ_FP32, &grid);
-                part = std::max(part, sizeof(uint64_t) * (size_t)(nq * parts * k_first));
-                mkeys = std::max(mkeys, sizeof(uint64_t) * (size_t)grid * tq * mfma_wide_cap(k_first));
-            }
+            reserve_wide(tq, scan_level == LVQ_FULL ? f.bits2 : 0);
         }
     } else {
         const int bits2 = scan_level == LVQ_FULL ? f.bits2 : 0;
@@ -1643,13 +1741,13 @@ int lvq::host_reserve(lvq_index *ix, hipStream_t s, int64_t max_nq, int32_t k_fi
             if (!q) continue;
             const int64_t tq = 32 * q;
             q16 = std::max(q16, (size_t)((max_nq + tq - 1) / tq) * tq * f.kpos * 2);
+            if (wide) {
+                reserve_wide(tq, bits2);
+                continue;
+            }
             for (int64_t nq = 1; nq <= max_nq; ++nq) {
-                const int64_t qtiles = (nq + tq - 1) / tq;
-                int64_t grid = 0;
-                const int64_t parts = wide ? scan_parts_wide(ix, qtiles, k_first, n_rows, prec, &grid)
-                                           : scan_parts_mfma(ix, qtiles, k_first, n_rows);
+                const int64_t parts = scan_parts_mfma(ix, (nq + tq - 1) / tq, k_first, n_rows);
                 part = std::max(part, sizeof(uint64_t) * (size_t)(nq * parts * k_first));
-                if (wide) mkeys = std::max(mkeys, sizeof(uint64_t) * (size_t)grid * tq * mfma_wide_cap(k_first));
             }
         }
         gthr = sizeof(uint32_t) * (size_t)max_nq;

@@ -132,6 +132,8 @@ struct ScanArgs {
     uint32_t *err;
     uint64_t *mkeys;         // wide matrix-core scan: per-workgroup key regions (mcap keys per query:
     int mcap, mks;           //   mks sorted best keys, then the keys appended since they were merged)
+    float *gmax;             // wide matrix-core scan, sample pass: nq x n_parts x 8 largest scores; else NULL
+    int64_t sample_rows;     //   rows scored at the start of every part
 };
 
 struct StoreArgs {
@@ -317,6 +319,10 @@ int mfma_capq(int qb, int n_means, int k, size_t lds_max);
 int mfma_wide_query_block(int bits1, int bits2, int kpos, int prec, int k, int n_means, size_t lds_max);
 int mfma_wide_sorted(int k);
 int mfma_wide_cap(int k);
+// The wide scan's sample pass: rows per round, and the shared bounds from its
+// maxima (groups per query, k <= groups <= 2048).
+int mfma_wide_round(int bits1, int bits2, int kpos, int prec);
+hipError_t launch_sample_bound(const float *gmax, int groups, int64_t nq, int k, uint32_t *gthr, hipStream_t s);
 hipError_t launch_scan_mfma_wide(const ScanArgs &a, int bits1, int bits2, int prec, int64_t grid, size_t lds_max,
                                  hipStream_t s);
 hipError_t launch_prep_scan(const void *q, int64_t nq, int dim, int kpos, int bits1, int qb, int prec,

@@ -392,3 +392,100 @@ def test_encode_runs_past_one_pass_of_means(L):
     assert torch.equal(ix.read_rows(slots[pick].contiguous())[0][:, 32:], want[pick][:, 32:])
     assert ix.sync() == 0
     ix.close()
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp16", "fp32"])
+@pytest.mark.parametrize("n,nq,k,kind", [
+    (2047, 5, 8, "plain"), (2048, 130, 10, "plain"), (4097, 33, 33, "plain"),   # few rounds; groups around k
+    (20_000, 300, 100, "plain"), (30_011, 1, 512, "plain"),                     # several tiles; large k
+    (12_345, 65, 20, "same"),                                                   # every row reaches the bound
+    (12_345, 65, 20, "few"),                                                    # fewer live rows than k
+    (12_345, 65, 20, "tail"),                                                   # live rows only at the list's end
+    (12_345, 65, 20, "rising")])                                                # every row better than the one before
+def test_sampled_bounds_keep_the_answers(L, prec, n, nq, k, kind):
+    """Matrix-core scans that start from a sample's bounds, against exact whole
+    numbers: sizes around the smallest samples, ties, dead rows, NaN queries;
+    an index with a memory budget takes none and answers the same."""
+    g = synth.rng(8400 + n + nq, k)
+    d = 96
+    X, Q = int_rows(g, n, d), int_queries(g, nq, d)
+    live = np.ones(n, bool)
+    if kind == "plain":
+        live[np.unique(g.integers(0, n, n // 9))] = False
+    elif kind == "same":
+        X[:] = X[0]
+    elif kind == "few":
+        live[:] = False
+        live[g.permutation(n)[:k - 3]] = True
+    elif kind == "tail":
+        live[:n - 40] = False
+    else:
+        X[:, 1:d - 1] = (np.arange(n) * 255 // n)[:, None]
+        Q[:] = np.abs(Q)
+    dead = np.flatnonzero(~live)
+    v = values(True, Q, X).astype(np.float64)
+    v[:, dead] = -np.inf
+    ids, val = best(True, v, k)
+    ids[~np.isfinite(val)] = -1
+    q = torch.from_numpy(Q).cuda().to(dict(bf16=torch.bfloat16, fp16=torch.float16, fp32=torch.float32)[prec])
+    if nq > 4:
+        q[4] = float("nan")
+        ids, val = np.delete(ids, 4, 0), np.delete(val, 4, 0)
+    for budget in (0, 1 << 33):
+        ix = L.Index(d, 8, 0, L.LVQ_IP, L.LVQ_SEQUENTIAL, capacity=n, means=np.zeros((1, d), np.float32),
+                     mem_budget_bytes=budget)
+        ix.insert(torch.from_numpy(X).cuda())
+        if len(dead):
+            ix.delete(torch.tensor(dead, dtype=torch.int32, device="cuda"))
+        ti, td = (t.cpu().numpy() for t in ix.topk(q, k))
+        assert ix.sync() == 0
+        if nq > 4:
+            assert (ti[4] == -1).all()
+            ti, td = np.delete(ti, 4, 0), np.delete(td, 4, 0)
+        np.testing.assert_array_equal(ti, ids)
+        np.testing.assert_array_equal(td.astype(np.float64), val)
+        ix.close()
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp32"])
+@pytest.mark.parametrize("d,b1,M", [(768, 4, 16), (512, 8, 3), (96, 8, 1)])
+def test_sampled_bounds_both_levels(L, d, b1, M, prec):
+    """Both levels, several means: a store scanned with a sample's bounds
+    answers, bit for bit, as an index under a memory budget that takes none;
+    so does a captured call whose stream has room for the sample, and one that
+    has not."""
+    g = synth.rng(8500 + d, M)
+    n, nq, k = 9000, 70, 15
+    mu = g.standard_normal((M, d)).astype(np.float32)
+    X = (mu[g.integers(0, M, n)] + g.standard_normal((n, d))).astype(np.float32)
+    x = torch.from_numpy(X).cuda()
+    q = torch.from_numpy(g.standard_normal((nq, d)).astype(np.float32)).cuda()
+    q = q.to(torch.bfloat16) if prec == "bf16" else q
+    res = []
+    for budget in (1 << 33, 0):
+        ix = L.Index(d, b1, 8, L.LVQ_IP, L.LVQ_TURBO, capacity=n, means=mu, mem_budget_bytes=budget)
+        ix.insert(x)
+        res.append(ix.topk(q, k, level=L.LVQ_FULL))
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
+    for warm_k in (k, 1):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            ix.topk(q, warm_k, level=L.LVQ_FULL)
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        try:
+            with torch.cuda.graph(graph, stream=s):
+                got = ix.topk(q, k, level=L.LVQ_FULL)
+        except L.LVQError:      # no room for the keys: refused
+            assert warm_k == 1
+            continue
+        for _ in range(3):
+            for t in got:
+                t.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            for a, b in zip(got, res[0]):
+                assert torch.equal(a, b)
+    assert ix.sync() == 0
+    ix.close()
