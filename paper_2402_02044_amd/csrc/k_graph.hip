@@ -14,8 +14,8 @@
 // levels re-rank); over float vectors (construction) it is the binary32
 // squared distance or inner product.
 //
-// Pruning: one workgroup per node.  Its candidates and current out-neighbours
-// are scored against it into LDS keys, sorted by one wave and deduplicated;
+// Pruning: one wave per node.  Its candidates and current out-neighbours
+// are scored against it into LDS keys, sorted and deduplicated;
 // the best remaining candidate x* is kept and every candidate that x* is at
 // least alpha times as similar to as the node is dropped, until R are kept.
 #include <algorithm>
@@ -87,22 +87,49 @@ __device__ __forceinline__ bool hash_contains(const int32_t *h, int32_t s, uint3
     return false;
 }
 
-// Similarity of two float vectors (one in LDS, one in global memory) by the
-// G lanes of a group (G = 4 or 16); every lane of the group returns the value.
-template <int METRIC, int G>
-__device__ __forceinline__ float sim_f32(const float *u, const float *x, int dim, int g)
+// Similarity of two float vectors by one lane, u the same for all lanes of the
+// wave (read through the scalar cache).  Sums run over j mod G in G chains
+// that meet as a quad's, an eight's and a row's lanes do in group_sum; VEC: x
+// is read 16 bytes at a time.
+typedef const __attribute__((address_space(4))) float UniformF;
+
+template <int METRIC, int G, bool VEC>
+__device__ __forceinline__ float sim_f32(const float *up, const float *x, int dim)
 {
-    float s = 0.0f;
-    for (int j = g; j < dim; j += G) {
-        const float v = x[j];
+    UniformF *u = (UniformF *)(uintptr_t)up;
+    float s[G];
+#pragma unroll
+    for (int e = 0; e < G; ++e) s[e] = 0.0f;
+    auto step = [](float a, float v, float &acc) {
         if constexpr (METRIC == LVQ_IP) {
-            s = fmaf(u[j], v, s);
+            acc = fmaf(a, v, acc);
         } else {
-            const float t = u[j] - v;
-            s = fmaf(t, t, s);
+            const float t = a - v;
+            acc = fmaf(t, t, acc);
+        }
+    };
+    int j = 0;
+#pragma unroll(32 / G)
+    for (; j + G <= dim; j += G) {
+#pragma unroll
+        for (int e = 0; e < G; e += 4) {
+            float4 v;
+            if constexpr (VEC) v = *reinterpret_cast<const float4 *>(x + j + e);
+            else v = make_float4(x[j + e], x[j + e + 1], x[j + e + 2], x[j + e + 3]);
+            step(u[j + e], v.x, s[e]);
+            step(u[j + e + 1], v.y, s[e + 1]);
+            step(u[j + e + 2], v.z, s[e + 2]);
+            step(u[j + e + 3], v.w, s[e + 3]);
         }
     }
-    return group_sum<G>(s);
+#pragma unroll
+    for (int e = 0; e < G; ++e)
+        if (j + e < dim) step(u[j + e], x[j + e], s[e]);
+#pragma unroll
+    for (int o = 1; o < G; o *= 2)
+#pragma unroll
+        for (int e = 0; e < G; e += 2 * o) s[e] += s[e + o];
+    return s[0];
 }
 
 // Similarity of one stored node to the query, by one lane.  LVQ rows: the
@@ -455,26 +482,28 @@ __global__ __launch_bounds__(64) void k_graph_search(GraphArgs a)
 
 // ---- neighbourhood pruning (Alg. 2) ----------------------------------------
 
-template <int METRIC, int G>
-__global__ __launch_bounds__(256) void k_graph_prune(PruneLaunch a)
+// One wavefront per node.  Lane l holds the sorted candidates l, 64 + l, ...;
+// which of them are left is a bit mask per 64 in scalar registers, so a pick is
+// a find-first-bit, and a round scores the candidates left, one per lane, with
+// no barrier.  Bound: the latency of the rows read in a round, hidden by the
+// other nodes' waves.  (Four waves per node met at three barriers a round and
+// left the neighbours, the repeats and each pick to one thread: building 5x10^4
+// x 96, R = 32, W = 64, 343 us a launch, 190 us now; 16,384 nodes of 96 candidates
+// take 900 us.)
+template <int METRIC, int G, bool VEC>
+__global__ __launch_bounds__(64) void k_graph_prune(PruneLaunch a)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int NG = 256 / G;
-    const int tid = threadIdx.x, wave = tid >> 6;
-    const int grp = tid / G, g = tid % G;
-    const int64_t i = blockIdx.x;
-    if (i >= a.m) return;
-    float *xv = reinterpret_cast<float *>(smem);   // the node (dim)
-    float *xs = xv + a.dim;                        // x* (dim)
-    __shared__ uint64_t keys[512];
+    constexpr int T = kPruneCap / 64;
+    static_assert(kPruneCap % 64 == 0 && kPruneChunk % 64 == 0 && kMaxDegree <= 64, "a lane per candidate and neighbour");
+    __shared__ uint64_t keys[kPruneCap];
     __shared__ int32_t cid[kPruneCap];
     __shared__ int32_t kept[kMaxDegree];
-    __shared__ uint8_t rm[kPruneCap];
-    __shared__ int s_n, s_kept, s_pick, s_unique;
-
-    const int32_t p = a.nodes[i];
+    const int lane = threadIdx.x;
+    const int64_t i = blockIdx.x;
+    if (i >= a.m) return;
+    const int32_t p = __builtin_amdgcn_readfirstlane(a.nodes[i]);
     if (p < 0 || p >= a.n) {
-        if (tid == 0) atomicOr(a.err, kErrBadSlot);
+        if (lane == 0) atomicOr(a.err, kErrBadSlot);
         return;
     }
     const uint8_t *del = a.deleted;
@@ -493,111 +522,119 @@ __global__ __launch_bounds__(256) void k_graph_prune(PruneLaunch a)
         c1 = c0 + a.cstride;
     }
     if (c0 < 0 || c1 < c0) {
-        if (tid == 0) atomicOr(a.err, kErrBadOffsets);
+        if (lane == 0) atomicOr(a.err, kErrBadOffsets);
         return;
     }
-    for (int j = tid; j < a.dim; j += 256) xv[j] = a.xf[(int64_t)p * a.dim + j];
-    if (tid == 0) s_kept = 0;
-    __syncthreads();
+    auto before = [](uint64_t m) {   // set bits of m below this lane
+        return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    };
+    const float *xp = a.xf + (int64_t)p * a.dim;
     // the current out-neighbours (kept in LDS across chunks)
-    if (tid == 0)
-        for (int r = 0; r < a.R; ++r) {
-            const int32_t y = a.graph[(int64_t)p * a.R + r];
-            if (y >= 0 && y < a.n && y != p && !(del && del[y])) kept[s_kept++] = y;
-        }
+    int nkept;
+    {
+        const int32_t y = lane < a.R ? a.graph[(int64_t)p * a.R + lane] : -1;
+        const bool ok = y >= 0 && y < a.n && y != p && !(del && del[y]);
+        const uint64_t m = __ballot(ok);
+        if (ok) kept[before(m)] = y;
+        nkept = __popcll(m);
+    }
     __syncthreads();
 
     int64_t cs = c0;   // next position block (kPruneChunk positions) to read
     for (;;) {
-        if (tid == 0) s_n = s_kept;
-        for (int r = tid; r < s_kept; r += 256) cid[r] = kept[r];
-        __syncthreads();
+        int nn = nkept;
+        if (lane < nkept) cid[lane] = kept[lane];
         // append whole position blocks, in order, while their candidates fit
         // beside the out-neighbours kept so far (the first block always fits:
         // R + kPruneChunk <= kPruneCap)
-        for (;;) {
-            const int have = s_n;   // last written before the preceding barrier
-            const int64_t j = cs + tid;
-            int32_t y = -1;
-            if (j < c1) {
-                if (del) {
-                    const int32_t v = a.graph[(int64_t)p * a.R + j / a.R];
-                    y = v >= 0 && v < a.n && del[v] ? a.graph[(int64_t)v * a.R + j % a.R] : -1;
-                    if (y >= 0 && y < a.n && del[y]) y = -1;
-                } else {
-                    y = a.cids[j];
+        while (cs < c1) {
+            int32_t y[kPruneChunk / 64];
+            uint64_t m[kPruneChunk / 64];
+            int cnt = 0;
+#pragma unroll
+            for (int b = 0; b < kPruneChunk / 64; ++b) {
+                const int64_t j = cs + 64 * b + lane;
+                y[b] = -1;
+                if (j < c1) {
+                    if (del) {
+                        const int32_t v = a.graph[(int64_t)p * a.R + j / a.R];
+                        y[b] = v >= 0 && v < a.n && del[v] ? a.graph[(int64_t)v * a.R + j % a.R] : -1;
+                        if (y[b] >= 0 && y[b] < a.n && del[y[b]]) y[b] = -1;
+                    } else {
+                        y[b] = a.cids[j];
+                    }
+                    if (!(y[b] >= 0 && y[b] < a.n && y[b] != p)) y[b] = -1;
                 }
-                if (!(y >= 0 && y < a.n && y != p)) y = -1;
+                m[b] = __ballot(y[b] >= 0);
+                cnt += __popcll(m[b]);
             }
-            const int cnt = __syncthreads_count(y >= 0);
-            if (cs >= c1 || have + cnt > kPruneCap) break;
-            if (y >= 0) cid[atomicAdd(&s_n, 1)] = y;
+            if (nn + cnt > kPruneCap) break;
+#pragma unroll
+            for (int b = 0; b < kPruneChunk / 64; ++b) {
+                if (y[b] >= 0) cid[nn + before(m[b])] = y[b];
+                nn += __popcll(m[b]);
+            }
             cs += kPruneChunk;
-            __syncthreads();
-        }
-        const int nn = s_n;
-        // similarities to the node
-        for (int c = grp; c < nn; c += NG) {
-            const int32_t y = cid[c];
-            const float v = sim_f32<METRIC, G>(xv, a.xf + (int64_t)y * a.dim, a.dim, g);
-            if (g == 0) keys[c] = make_key(v, y, METRIC);
         }
         __syncthreads();
-        if (wave == 0 && nn > 0) wave_compact(keys, nn, nn, nullptr);   // nn <= 320: register sort
+        // similarities to the node
+        for (int c = lane; c < nn; c += 64) {
+            const int32_t y = cid[c];
+            keys[c] = make_key(sim_f32<METRIC, G, VEC>(xp, a.xf + (int64_t)y * a.dim, a.dim), y, METRIC);
+        }
+        __syncthreads();
+        if (nn > 0) wave_compact(keys, nn, nn, nullptr);   // nn <= 320: register sort
         __syncthreads();
         // equal keys (the same node) are adjacent
-        for (int c = tid; c < nn; c += 256) rm[c] = c > 0 && keys[c] == keys[c - 1];
-        __syncthreads();
-        if (tid == 0) {
-            int u = 0;
-            for (int c = 0; c < nn; ++c) u += !rm[c];
-            s_unique = u;
-            s_kept = 0;
-            s_pick = -1;
+        uint64_t key[T], left[T];
+        int unique = 0;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int c = 64 * t + lane;
+            key[t] = c < nn ? keys[c] : kNoKey;
+            left[t] = __ballot(c < nn && !(c > 0 && keys[c - 1] == key[t]));
+            unique += __popcll(left[t]);
         }
-        __syncthreads();
-        if (!a.always && s_unique <= a.R) {
-            if (tid == 0)
-                for (int c = 0; c < nn; ++c)
-                    if (!rm[c]) kept[s_kept++] = (int32_t)(uint32_t)keys[c];
-            __syncthreads();
+        nkept = 0;
+        if (!a.always && unique <= a.R) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                if ((left[t] >> lane) & 1) kept[nkept + before(left[t])] = (int32_t)(uint32_t)key[t];
+                nkept += __popcll(left[t]);
+            }
         } else {
-            int pos = 0;
             for (;;) {
-                if (tid == 0) {
-                    int c = pos;
-                    while (c < nn && rm[c]) ++c;
-                    if (c < nn) {
-                        kept[s_kept++] = (int32_t)(uint32_t)keys[c];
-                        rm[c] = 1;
-                        s_pick = s_kept < a.R ? c : -1;
-                    } else {
-                        s_pick = -1;
+                int c = -1;
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+                    if (c < 0 && left[t]) {
+                        c = 64 * t + __builtin_ctzll(left[t]);
+                        left[t] &= left[t] - 1;
                     }
-                }
-                __syncthreads();
-                const int c = s_pick;
                 if (c < 0) break;
-                pos = c + 1;
-                const int32_t xstar = (int32_t)(uint32_t)keys[c];
-                for (int j = tid; j < a.dim; j += 256) xs[j] = a.xf[(int64_t)xstar * a.dim + j];
-                __syncthreads();
-                for (int e = pos + grp; e < nn; e += NG) {
-                    if (rm[e]) continue;   // uniform within the group
-                    const int32_t y = (int32_t)(uint32_t)keys[e];
-                    const float t = sim_f32<METRIC, G>(xs, a.xf + (int64_t)y * a.dim, a.dim, g);
-                    const float sp = key_score(keys[e], METRIC);
-                    const float at = a.alpha * t;
-                    const bool drop = METRIC == LVQ_L2 ? at <= sp : at >= sp;
-                    if (g == 0 && drop) rm[e] = 1;
+                const int32_t xstar = __builtin_amdgcn_readfirstlane((int32_t)(uint32_t)keys[c]);
+                if (lane == 0) kept[nkept] = xstar;
+                if (++nkept >= a.R) break;
+                const float *xs = a.xf + (int64_t)xstar * a.dim;
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    if (!left[t]) continue;
+                    bool drop = false;
+                    if ((left[t] >> lane) & 1) {
+                        const int32_t y = (int32_t)(uint32_t)key[t];
+                        const float v = sim_f32<METRIC, G, VEC>(xs, a.xf + (int64_t)y * a.dim, a.dim);
+                        const float sp = key_score(key[t], METRIC);
+                        const float at = a.alpha * v;
+                        drop = METRIC == LVQ_L2 ? at <= sp : at >= sp;
+                    }
+                    left[t] &= ~__ballot(drop);
                 }
-                __syncthreads();
             }
         }
         __syncthreads();
         if (cs >= c1) break;
     }
-    for (int r = tid; r < a.R; r += 256) a.graph[(int64_t)p * a.R + r] = r < s_kept ? kept[r] : -1;
+    if (lane < a.R) a.graph[(int64_t)p * a.R + lane] = lane < nkept ? kept[lane] : -1;
 }
 
 // ---- reverse edges ----------------------------------------------------------
@@ -805,11 +842,16 @@ hipError_t launch_graph_prune(const PruneLaunch &l, hipStream_t s)
     if (l.m <= 0) return hipSuccess;
     if (l.R < 1 || l.R > kMaxDegree || l.dim < 1 || l.dim > kGraphMaxDim || l.m > 0x7FFFFFFF)
         return hipErrorInvalidValue;
-    const size_t lds = (size_t)2 * l.dim * 4;
-    void (*kern)(PruneLaunch) = l.dim <= 128
-        ? (l.metric == LVQ_IP ? k_graph_prune<LVQ_IP, 4> : k_graph_prune<LVQ_L2, 4>)
-        : (l.metric == LVQ_IP ? k_graph_prune<LVQ_IP, 16> : k_graph_prune<LVQ_L2, 16>);
-    hipLaunchKernelGGL(kern, dim3((unsigned)l.m), dim3(256), lds, s, l);
+    // 16-byte reads where every row starts at one
+    const bool vec = l.dim % 4 == 0 && reinterpret_cast<uintptr_t>(l.xf) % 16 == 0;
+    auto pick = [&](auto metric) -> void (*)(PruneLaunch) {
+        constexpr int M = decltype(metric)::value;
+        if (l.dim <= 128) return vec ? k_graph_prune<M, 4, true> : k_graph_prune<M, 4, false>;
+        return vec ? k_graph_prune<M, 16, true> : k_graph_prune<M, 16, false>;
+    };
+    void (*kern)(PruneLaunch) = l.metric == LVQ_IP ? pick(std::integral_constant<int, LVQ_IP>{})
+                                                   : pick(std::integral_constant<int, LVQ_L2>{});
+    hipLaunchKernelGGL(kern, dim3((unsigned)l.m), dim3(64), 0, s, l);
     return hipGetLastError();
 }
 

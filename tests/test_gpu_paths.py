@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import synth
 
 pytestmark = pytest.mark.gpu
@@ -489,3 +490,48 @@ def test_sampled_bounds_both_levels(L, d, b1, M, prec):
                 assert torch.equal(a, b)
     assert ix.sync() == 0
     ix.close()
+
+
+@pytest.mark.parametrize("d", [1, 3, 4, 31, 96, 97, 128, 129, 132, 144, 203])
+@pytest.mark.parametrize("metric,alpha,R", [(0, 1.25, 7), (1, 0.875, 64), (0, 1.25, 1)])
+def test_prune_edges(L, metric, alpha, R, d):
+    """Pruning with whole-number vectors against the oracle, exactly: candidate
+    counts around a wave and a group of positions, none at all, repeats, the node
+    itself and invalid ids among them; dimensions around the four and sixteen
+    chains of a sum, rows that start at 16 bytes and rows that do not."""
+    g = synth.rng(8600 + d, metric + R)
+    n = 700
+    lens = [0, 1, 63, 64, 65, 128, 200, 256, 257, 700]
+    m = len(lens)
+    X = g.integers(-6, 7, (n, d)).astype(np.float32)
+    graph = g.integers(-1, n, (n, R)).astype(np.int32)
+    nodes = g.choice(n, m, replace=False).astype(np.int32)
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    cand = g.integers(-1, n, int(offs[-1])).astype(np.int32)
+    for i in range(m):
+        if lens[i] > 4:
+            cand[offs[i]], cand[offs[i] + 1], cand[offs[i] + 2] = nodes[i], cand[offs[i] + 3], n
+    want = graph.copy()
+    for i, p in enumerate(nodes):
+        c = cand[offs[i]:offs[i + 1]]
+        cur, pos = [int(v) for v in graph[p] if v >= 0 and v != p], 0
+        while True:
+            group = []
+            while pos < len(c):
+                valid = [int(y) for y in c[pos:pos + 256] if 0 <= y < n and y != p]
+                if len(cur) + len(group) + len(valid) > 320:
+                    break
+                group += valid
+                pos += 256
+            cur = oracle.robust_prune(metric, X, int(p), group, cur, alpha, R)
+            if pos >= len(c):
+                break
+        want[p] = cur + [-1] * (R - len(cur))
+    flat = torch.zeros(n * d + 1, device="cuda")
+    for start in (0, 1):
+        x = flat[start:start + n * d].view(n, d)
+        x.copy_(torch.from_numpy(X))
+        gd = torch.from_numpy(graph).cuda()
+        L.graph_prune(x, torch.from_numpy(nodes).cuda(), torch.from_numpy(offs).cuda(), torch.from_numpy(cand).cuda(),
+                      gd, alpha, metric)
+        np.testing.assert_array_equal(gd.cpu().numpy(), want)
