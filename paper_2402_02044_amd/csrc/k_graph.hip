@@ -30,6 +30,7 @@ constexpr int kMaxHash = 16384;   // seen-set hash slots per query (int32 slot o
 constexpr int kMaxDegree = kGraphMaxDegree;
 constexpr int kMaxWindow = 256;
 constexpr int kPruneCap = kPruneChunk + kMaxDegree;   // candidates of one merge
+constexpr int kFewKeys = 24;      // new keys of a search step merged one by one
 constexpr int kFloat = 0;                             // MODE of float vectors
 
 struct GraphArgs {
@@ -153,9 +154,12 @@ __device__ __forceinline__ float score_rows(const GraphArgs &a, const float *qt,
     float s = 0.0f;
     // one 16-byte chunk; the mask is applied only in the chunks from cpad on,
     // which run in a loop of their own (same order of accumulation)
+    uint4 next = code[0];   // a row's pieces are read one ahead
     auto chunk = [&](int c, auto masked_tag) {
         constexpr bool masked = decltype(masked_tag)::value;
-        const uint4 v = code[c];
+        const uint4 v = next;
+        next = code[min(c + 1, a.kchunks - 1)];
+        __builtin_amdgcn_sched_barrier(0);
         const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -288,6 +292,14 @@ __device__ __forceinline__ void wave_sort64(uint64_t &v, int lane)
 // among the new keys plus the number of set keys below it, a set key moves
 // down by the number of new keys below it.  Keys landing below W form the new
 // set; the smallest position of an unexplored key is the next node.
+// Most steps of a full set bring few keys below its W-th: those are not sorted
+// but broadcast one after the other and ranked by comparisons in registers, up
+// to kFewKeys of them (the sort and the searches cost as much as about 30: with
+// 40 the cases below ran 1 to 4% slower, with all of them sorted 6 to 20%).
+// Bound: one query alone by the latency of a step (10^5 x 96, R = 64, W = 96: 494 us
+// before, 418 now), 10^4 of them by vector-ALU issue, of which lanes whose
+// neighbour was seen before have no use (1746 and 1650 us; 4-bit 2x10^4, R = 32:
+// 1773 and 1525).  Reading the runner-up's neighbours ahead gave nothing.
 template <int B1, int METRIC>
 __global__ __launch_bounds__(64) void k_graph_search(GraphArgs a)
 {
@@ -340,6 +352,66 @@ __global__ __launch_bounds__(64) void k_graph_search(GraphArgs a)
     // Merge the lanes' keys (kNoKey where none) into the set; returns the
     // number of distinct new nodes.
     auto merge = [&](uint64_t key) -> int {
+        const uint64_t fresh = __ballot(key != kNoKey);
+        if (__popcll(fresh) <= kFewKeys) {
+            // Few keys: each is broadcast in turn and ranked against the set (in
+            // registers, a position per lane) and the other new keys.
+            __syncthreads();   // the explored mark
+            uint64_t c[kMaxWindow / 64];
+            int up[kMaxWindow / 64];   // new keys below each set key
+#pragma unroll
+            for (int t = 0; t < kMaxWindow / 64; ++t) {
+                const int i = 64 * t + lane;
+                c[t] = i < qn ? cur[i] : kNoKey;
+                up[t] = 0;
+            }
+            uint64_t todo = fresh, mine = fresh;
+            int p = 0, nn = 0;
+            while (todo) {
+                const int src = __builtin_ctzll(todo);
+                const uint64_t k = readlane_u64(key, src);
+                // the same node again, in later lanes: dropped
+                const uint64_t same = __ballot(key == k);
+                todo &= ~same;
+                mine &= ~(same & ~(1ull << src));
+                ++nn;
+                int below = 0;
+#pragma unroll
+                for (int t = 0; t < kMaxWindow / 64; ++t) {
+                    if (64 * t >= qn) break;
+                    const bool lt = c[t] < k;
+                    below += __popcll(__ballot(lt));
+                    up[t] += !lt;
+                }
+                p += lane == src ? below : k < key;
+            }
+            int best = 1 << 30;
+            bool full = false;
+            if (((mine >> lane) & 1) && p < W) {
+                nxt[p] = key;
+                best = p;
+                full = hash_insert(hset, key_node(key), hn) < 0;
+            }
+#pragma unroll
+            for (int t = 0; t < kMaxWindow / 64; ++t) {
+                const int at = 64 * t + lane + up[t];
+                if (64 * t + lane < qn && at < W) {
+                    nxt[at] = c[t];
+                    if (!(c[t] & 1ull) && at < best) best = at;
+                }
+            }
+            if (__ballot(full)) {
+                if (lane == 0) atomicOr(a.err, kErrOverflow);
+                stop = true;
+            }
+            __syncthreads();
+            pick = (int)wave_min_u64((uint64_t)(uint32_t)best);
+            qn = min(W, qn + nn);
+            uint64_t *t = cur;
+            cur = nxt;
+            nxt = t;
+            return nn;
+        }
         wave_sort64(key, lane);
         const uint32_t plo = __shfl_up((uint32_t)key, 1, 64), phi = __shfl_up((uint32_t)(key >> 32), 1, 64);
         const bool valid = key != kNoKey && !(lane > 0 && key == (((uint64_t)phi << 32) | plo));
@@ -441,7 +513,7 @@ __global__ __launch_bounds__(64) void k_graph_search(GraphArgs a)
             }
             continue;
         }
-        merge(key);
+        merge(key < worst ? key : kNoKey);
     }
 
     // the k best live keys, in order

@@ -535,3 +535,33 @@ def test_prune_edges(L, metric, alpha, R, d):
         L.graph_prune(x, torch.from_numpy(nodes).cuda(), torch.from_numpy(offs).cuda(), torch.from_numpy(cand).cuda(),
                       gd, alpha, metric)
         np.testing.assert_array_equal(gd.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("W,k,R", [(1, 1, 3), (10, 10, 23), (63, 10, 24), (64, 5, 25), (65, 20, 64), (130, 10, 40),
+                                   (256, 64, 64)])
+@pytest.mark.parametrize("metric_ip", [False, True])
+def test_search_merges_few_and_many_keys(L, metric_ip, W, k, R):
+    """Search steps that bring no, a few and a whole wave of new keys, with
+    repeated neighbours, missing ones and ties, follow the oracle exactly on
+    whole-number rows, in windows of one to four keys per lane."""
+    g = synth.rng(8700 + W, R)
+    n, d, nq = 900, 35, 12
+    X, Q = int_rows(g, n, d), int_queries(g, nq, d)
+    graph = g.integers(0, n, (n, R)).astype(np.int32)
+    graph[:, R // 2] = graph[:, 0]
+    graph[g.random((n, R)) < 0.1] = -1
+    graph[::5, 1:] = -1
+    entries = g.choice(n, 5, replace=False).astype(np.int32)
+    v = values(metric_ip, Q, X).astype(np.float64)
+    ix = store(L, X, metric_ip)
+    ids, dist, explored = (t.cpu().numpy() for t in ix.graph_search(
+        torch.from_numpy(Q).cuda(), torch.from_numpy(graph).cuda(), torch.from_numpy(entries).cuda(), W, k))
+    assert ix.sync() == 0
+    for i in range(nq):
+        os_, ov, ne = oracle._walk(lambda s: v[i][np.asarray(s)], oracle.IP if metric_ip else oracle.L2, graph, entries,
+                                   W, k)
+        got = ids[i][ids[i] >= 0]
+        np.testing.assert_array_equal(got, os_)
+        np.testing.assert_array_equal(dist[i][:len(got)].astype(np.float64), ov)
+        assert explored[i, 0] == ne
+    ix.close()
