@@ -572,7 +572,7 @@ __global__ __launch_bounds__(64) void k_graph_prune(PruneLaunch a)
     __shared__ int32_t kept[kMaxDegree];
     const int lane = threadIdx.x;
     const int64_t i = blockIdx.x;
-    if (i >= a.m) return;
+    if (i >= a.m || (a.m_dev && i >= *a.m_dev)) return;
     const int32_t p = __builtin_amdgcn_readfirstlane(a.nodes[i]);
     if (p < 0 || p >= a.n) {
         if (lane == 0) atomicOr(a.err, kErrBadSlot);

@@ -1920,11 +1920,10 @@ namespace {
 
 int graph_device_lds(size_t *out)
 {
-    int dev = 0;
-    hipDeviceProp_t prop;
+    int dev = 0, bytes = 0;
     LVQ_HIP(hipGetDevice(&dev));
-    LVQ_HIP(hipGetDeviceProperties(&prop, dev));
-    *out = prop.sharedMemPerBlock;
+    LVQ_HIP(hipDeviceGetAttribute(&bytes, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+    *out = (size_t)bytes;
     return LVQ_OK;
 }
 
@@ -1935,25 +1934,33 @@ int graph_kernel_error(uint32_t e)
     return LVQ_OK;   // a search that stopped at the seen-set capacity still yields candidates
 }
 
-// Device buffers of one construction call, released on every exit path.
+// Device buffers of one construction call: parts of one allocation (each
+// allocation and release costs about as much as a small batch), released on
+// every exit path.
 struct GraphScratch {
-    std::vector<void *> bufs;
+    void *mem = nullptr;
+    size_t bytes = 0;
+    std::vector<std::pair<void **, size_t>> parts;
     hipStream_t s;
     explicit GraphScratch(hipStream_t st) : s(st) {}
     template <typename T>
-    int alloc(T **p, size_t count)
+    void want(T **p, size_t count)
     {
         *p = nullptr;
-        void *q = nullptr;
-        LVQ_HIP(hipMalloc(&q, std::max<size_t>(count, 1) * sizeof(T)));
-        bufs.push_back(q);
-        *p = static_cast<T *>(q);
+        parts.emplace_back(reinterpret_cast<void **>(p), bytes);
+        bytes += (std::max<size_t>(count, 1) * sizeof(T) + 255) / 256 * 256;
+    }
+    int get()
+    {
+        LVQ_HIP(hipMalloc(&mem, bytes));
+        for (auto &p : parts) *p.first = static_cast<char *>(mem) + p.second;
         return LVQ_OK;
     }
     ~GraphScratch()
     {
+        if (!mem) return;
         (void)hipStreamSynchronize(s);
-        for (void *q : bufs) (void)hipFree(q);
+        (void)hipFree(mem);
     }
 };
 
@@ -1983,12 +1990,17 @@ int graph_update(const float *x_dev, int64_t n, int dim, int metric, const std::
     int64_t *offs, *scan;
     uint32_t *err;
     const int64_t nb = (n + 2047) / 2048;
-    if ((rc = sc.alloc(&order_d, (size_t)count)) || (rc = sc.alloc(&res, (size_t)(B * window))) ||
-        (rc = sc.alloc(&cnt, (size_t)n)) || (rc = sc.alloc(&offs, (size_t)n + 1)) ||
-        (rc = sc.alloc(&scan, (size_t)nb + 1)) || (rc = sc.alloc(&rev, (size_t)(B * R))) ||
-        (rc = sc.alloc(&touched, (size_t)(B * R))) || (rc = sc.alloc(&ntouched, 1)) ||
-        (rc = sc.alloc(&entry_d, 1)) || (rc = sc.alloc(&err, 1)))
-        return rc;
+    sc.want(&order_d, (size_t)count);
+    sc.want(&res, (size_t)(B * window));
+    sc.want(&cnt, (size_t)n);
+    sc.want(&offs, (size_t)n + 1);
+    sc.want(&scan, (size_t)nb + 1);
+    sc.want(&rev, (size_t)(B * R));
+    sc.want(&touched, (size_t)(B * R));
+    sc.want(&ntouched, 1);
+    sc.want(&entry_d, 1);
+    sc.want(&err, 1);
+    if ((rc = sc.get())) return rc;
     LVQ_HIP(hipMemcpyAsync(order_d, order.data(), sizeof(int32_t) * (size_t)count, hipMemcpyHostToDevice, s));
     LVQ_HIP(hipMemcpyAsync(entry_d, &entry, sizeof(int32_t), hipMemcpyHostToDevice, s));
     LVQ_HIP(launch_graph_clear_rows(graph_dev, R, n, nullptr, order_d, count, s));
@@ -2034,12 +2046,12 @@ int graph_update(const float *x_dev, int64_t n, int dim, int metric, const std::
             p.err = err;
             LVQ_HIP(launch_graph_prune(p, s));
             LVQ_HIP(launch_reverse_edges(graph_dev, R, nodes, bs, n, cnt, offs, scan, rev, touched, ntouched, s));
-            int32_t nt = 0;
-            LVQ_HIP(hipMemcpyAsync(&nt, ntouched, sizeof(nt), hipMemcpyDeviceToHost, s));
-            LVQ_HIP(hipStreamSynchronize(s));
+            // (the host does not wait for the count: a wave per possible node is
+            // launched, and those past it end at once)
             PruneLaunch r = p;
             r.nodes = touched;
-            r.m = nt;
+            r.m = std::min<int64_t>(n, bs * R);
+            r.m_dev = ntouched;
             r.coffs = offs;
             r.by_node = 1;
             r.cids = rev;
@@ -2071,7 +2083,8 @@ int lvq_graph_prune(const float *x_dev, int64_t n, int32_t dim, int32_t metric, 
     hipStream_t s = (hipStream_t)stream;
     GraphScratch sc(s);
     uint32_t *err = nullptr;
-    int rc = sc.alloc(&err, 1);
+    sc.want(&err, 1);
+    int rc = sc.get();
     if (rc) return rc;
     LVQ_HIP(launch_fill_u32(err, 0, 1, s));
     PruneLaunch l{};
@@ -2145,7 +2158,10 @@ int lvq_graph_delete(const float *x_dev, int64_t n, int32_t dim, int32_t metric,
     int32_t *affected, *count;
     uint32_t *err;
     int rc;
-    if ((rc = sc.alloc(&affected, (size_t)n)) || (rc = sc.alloc(&count, 1)) || (rc = sc.alloc(&err, 1))) return rc;
+    sc.want(&affected, (size_t)n);
+    sc.want(&count, 1);
+    sc.want(&err, 1);
+    if ((rc = sc.get())) return rc;
     LVQ_HIP(launch_fill_u32(err, 0, 1, s));
     LVQ_HIP(launch_graph_affected(graph_dev, degree, n, deleted_dev, affected, count, s));
     int32_t na = 0;

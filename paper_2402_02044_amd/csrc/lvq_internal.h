@@ -248,7 +248,8 @@ struct PruneLaunch {
     int dim, metric;
     int64_t n;
     const int32_t *nodes;
-    int64_t m;
+    int64_t m;              // nodes, or an upper bound of them with
+    const int32_t *m_dev;   //   their number on the device (else NULL)
     const int64_t *coffs;
     int by_node;
     const int32_t *cids;
