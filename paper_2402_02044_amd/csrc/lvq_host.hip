@@ -1143,7 +1143,9 @@ static ScanSample scan_sample(const lvq_index *ix, int64_t qtiles, int32_t k, in
     const int64_t round = mfma_wide_round(f.bits1, bits2, f.kpos, prec);
     const bool f32 = prec == LVQ_FP32;
     const double row_cost = f32 ? 8.0 : 1.0;
-    const double want = std::sqrt(80.0 * 512.0 / (f.kpos * row_cost) * (double)n_rows * k);
+    // (a part's own bound catches up with larger samples: 10^4 queries x 5x10^6 x
+    // 512, k = 100: 51.8 ms with 65k rows, 52.5 with 200k and with none)
+    const double want = std::min(65536.0, std::sqrt(80.0 * 512.0 / (f.kpos * row_cost) * (double)n_rows * k));
     const int64_t most = n_rows / (2 * round);   // at most half the rows
     const int64_t slots = std::max<int64_t>(8, ix->n_cu / 8 * 8);
     // (a pass that leaves half the chip idle costs no more with larger samples)
@@ -1172,7 +1174,10 @@ static ScanSample scan_sample(const lvq_index *ix, int64_t qtiles, int32_t k, in
 // for staging the queries and the final merge (10^5 x 512, 1000 queries: 8 x 32
 // tiles 199 us, 8 x 64 251; 10^6 x 96, 300 queries: 3 x 64 tiles 271, 3 x 256 278) and
 // 16 for each key that passes: R k / S per query while R is less than the S sampled rows,
-// k (1 + ln(R / S)) beyond.  Without a sample a part's bound starts loose: a 32 x 32
+// k (1 + ln(R / S)) beyond.  Every tile after a workgroup's first adds 2.5%: the
+// workgroups of an XCD then no longer read the same rows at the same time (10^4
+// queries x 5x10^6 x 512: 79 x 3 tiles 51.8 ms, x 6 52.2, x 16 53.2, x 29 58.6; 4096 x
+// 2x10^6: 32 x 8 8.98 ms, x 16 9.06, x 32 9.51; FP32 rows, an eighth of it).  Without a sample a part's bound starts loose: a 32 x 32
 // block of scores holds a key beating the running k-th best of t rows with
 // probability about min(1, 1024 k / t), so the blocks that append add about
 // 512 k (1 + ln(R / 1024 k)) rows' worth, and 10,240 for the rest.
@@ -1197,7 +1202,7 @@ static int64_t scan_parts_wide(const lvq_index *ix, int64_t qtiles, int32_t k, i
         const double row_cost = prec == LVQ_FP32 ? 8.0 : 1.0;
         const double extra = sm.parts ? 2200.0 + 16.0 * k * (rows < sampled ? rows / sampled : 1.0 + std::log(rows / sampled))
                                       : 10240.0 + 0.5 * warm * (1.0 + std::log(std::max(1.0, rows / warm)));
-        const double cost = (double)iters * (rows + extra / row_cost);
+        const double cost = (double)iters * (rows + extra / row_cost) * (sm.parts ? 1.0 + 0.025 / row_cost * (double)(iters - 1) : 1.0);
         if (p == 1 || cost < best) {
             best = cost;
             parts = p;
