@@ -301,6 +301,15 @@ int order_shape(const Format &f, void *(*lookup)(int, int, int), int bits2, int 
     return best;
 }
 
+// A shape can score the rows of a format at a level: it is instantiated, and a
+// pipelined one reads the whole row in its one round.
+bool shape_fits(const Format &f, void *(*lookup)(int, int, int), int bits2, int variant, int shape)
+{
+    if (shape < 0 || shape >= num_tile_shapes() || !lookup(bits2, variant, shape)) return false;
+    TileShape t = tile_shape(shape);
+    return !t.pipe || t.g * t.ch * t.nch >= f.kchunks * 16;
+}
+
 // Default tile shape: the layout measured fastest among those that give every
 // value with the order of sums of order_shape, so that results do not depend
 // on the choice.  Microseconds for 3.0e6 pairs of 3,000 ragged lists, top-10
@@ -342,16 +351,10 @@ int default_shape(const Format &f, void *(*lookup)(int, int, int), int bits2, in
         if (variant >= 3) pick = bytes <= 128 ? 33 : 10;
         else pick = one ? 18 : 10;
     }
-    if (pick == base || !lookup(bits2, variant, pick)) return base;
+    // (rows of 1040 to 1152 bytes take the order of three rounds of 384)
+    if (pick == base || !shape_fits(f, lookup, bits2, variant, pick)) return base;
     if (ip && bytes < t.g * t.ch * t.nch) *idle = t.ch * 8 / f.bits1;
     return pick;
-}
-
-bool shape_fits(const Format &f, void *(*lookup)(int, int, int), int bits2, int variant, int shape)
-{
-    if (shape < 0 || shape >= num_tile_shapes() || !lookup(bits2, variant, shape)) return false;
-    TileShape t = tile_shape(shape);
-    return !t.pipe || t.g * t.ch * t.nch >= f.kchunks * 16;
 }
 
 }  // namespace

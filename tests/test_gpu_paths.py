@@ -565,3 +565,50 @@ def test_search_merges_few_and_many_keys(L, metric_ip, W, k, R):
         np.testing.assert_array_equal(dist[i][:len(got)].astype(np.float64), ov)
         assert explored[i, 0] == ne
     ix.close()
+
+
+@pytest.mark.parametrize("d,b1,b2", [(1040, 8, 0), (1088, 8, 8), (1152, 8, 8), (1168, 8, 0), (2080, 4, 8), (2304, 4, 8),
+                                     (2304, 4, 0)])
+@pytest.mark.parametrize("ip", [0, 1])
+@pytest.mark.parametrize("M", [1, 3])
+def test_lists_of_long_rows(L, d, b1, b2, ip, M):
+    """Rows past one round of every pipelined tile shape (1040 to 1152 code
+    bytes take the order of sums of a shape of three rounds), by the default
+    shape: lists whole and split, the allocation-free form and the probe,
+    against the oracle."""
+    from lvq_check import check_topk, check_values, pair_reference
+    g = synth.rng(8100 + d + b1, b2 + 2 * ip + M)
+    n, nq, k = 300, 3, 10
+    X = g.standard_normal((n, d)).astype(np.float32)
+    Q = g.standard_normal((nq, d)).astype(np.float32)
+    means = (X[:M] * 0.25).astype(np.float32)
+    metric = oracle.IP if ip else oracle.L2
+    fmt = oracle.Format(d, b1, b2, oracle.SEQUENTIAL)
+    rows, resid, _ = oracle.encode_rows(fmt, X, means)
+    ix = L.Index(d, b1, b2, L.LVQ_IP if ip else L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=n, means=means)
+    ix.insert(torch.from_numpy(X).cuda())
+    offs = np.array([0, n, n + 1, n + 98], np.int64)
+    ids = np.concatenate([g.permutation(n), [7], g.permutation(n)[:97]]).astype(np.int32)
+    args = (torch.from_numpy(Q).cuda(), torch.from_numpy(offs).cuda(), torch.from_numpy(ids).cuda())
+    every = np.arange(n, dtype=np.int32)
+    for level in ([L.LVQ_PRIMARY, L.LVQ_FULL] if b2 else [L.LVQ_PRIMARY]):
+        ref, tol = pair_reference(fmt, metric, level, Q, rows, resid, means, offs, ids)
+        check_values(ix.distances(*args, level=level, k=0)[0].cpu().numpy(), ref, tol)
+        dist = torch.empty(len(ids), device="cuda")
+        ti, td = torch.empty(nq, k, dtype=torch.int32, device="cuda"), torch.empty(nq, k, device="cuda")
+        for form in (L.lvq_distances, L.lvq_distances_noalloc):
+            form(ix.handle, args[0].data_ptr(), nq, args[1].data_ptr(), args[2].data_ptr(), len(ids), level,
+                 dist.data_ptr(), k, ti.data_ptr(), td.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            assert ix.sync() == 0
+            check_values(dist.cpu().numpy(), ref, tol)
+            for i in range(nq):
+                c = slice(offs[i], offs[i + 1])
+                check_topk(metric, ti[i].cpu().numpy(), td[i].cpu().numpy(), ids[c], ref[c], tol[c], k)
+        all_offs = np.arange(nq + 1, dtype=np.int64) * n
+        ref, tol = pair_reference(fmt, metric, level, Q, rows, resid, means, all_offs, np.tile(every, nq))
+        _, pi, pd = ix.probe_topk(args[0], M, k, level=level)
+        for i in range(nq):
+            c = slice(i * n, (i + 1) * n)
+            check_topk(metric, pi[i].cpu().numpy(), pd[i].cpu().numpy(), every, ref[c], tol[c], k)
+    assert ix.sync() == 0
+    ix.close()
