@@ -27,8 +27,9 @@
  *    captured call allocates nothing and otherwise fails with
  *    LVQ_ERR_INVALID_ARG); lvq_distances_noalloc needs no such call.  A
  *    captured call replays at the store epoch of capture and does not order
- *    itself after store updates on other streams; no other entry point may
- *    be captured.  After a capture the stream's workspace is fixed for the
+ *    itself after store updates on other streams.  lvq_encode, which writes
+ *    only the caller's buffers, may be captured too; no other entry point
+ *    may.  After a capture the stream's workspace is fixed for the
  *    index's life, so that no replay reads or writes freed memory: a later
  *    call on that stream that would need a larger workspace fails with
  *    LVQ_ERR_INVALID_ARG (use another stream).  The occupied-slot list a

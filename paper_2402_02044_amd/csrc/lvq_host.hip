@@ -176,6 +176,16 @@ int begin_call(lvq_index *ix, hipStream_t s)
     return LVQ_OK;
 }
 
+// The same question for a call that keeps no record of a capture: updates and
+// lvq_encode, which leave ix->capturing false.
+bool stream_captures(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;   // (another stream's capture forbids the question: nothing is allocated)
+}
+
 // Make work on `s` wait for the latest store update issued on another stream.
 int order_after_updates(lvq_index *ix, hipStream_t s)
 {
@@ -577,18 +587,14 @@ static int encode_common(lvq_index *ix, const float *x, int64_t n, uint8_t *rows
     // room for the ids (this stream's own buffer; in a captured call or under a
     // memory budget, which it would take from the queries, the encoder searches).
     int32_t *buf = nullptr;
-    if (encode_assigns(n, ix->f.dim, ix->n_means)) {
-        int rc = begin_call(ix, s);
-        if (rc) return rc;
-        if (!ix->capturing && ix->cfg.mem_budget_bytes <= 0) {
-            Workspace &w = workspace(ix, s);
-            size_t room = 4096;   // (doubled, so that growing batches seldom grow the buffer)
-            while ((int64_t)room < std::min<int64_t>(n, kAssignRun)) room *= 2;
-            if (dev_alloc(ix, w.assign, sizeof(int32_t) * room) == LVQ_OK)
-                buf = P<int32_t>(w.assign);
-            else
-                (void)hipGetLastError();   // the call goes on without it
-        }
+    if (encode_assigns(n, ix->f.dim, ix->n_means) && !stream_captures(s) && ix->cfg.mem_budget_bytes <= 0) {
+        Workspace &w = workspace(ix, s);
+        size_t room = 4096;   // (doubled, so that growing batches seldom grow the buffer)
+        while ((int64_t)room < std::min<int64_t>(n, kAssignRun)) room *= 2;
+        if (dev_alloc(ix, w.assign, sizeof(int32_t) * room) == LVQ_OK)
+            buf = P<int32_t>(w.assign);
+        else
+            (void)hipGetLastError();   // the call goes on without it
     }
     if (!buf) {
         LVQ_HIP(launch_encode(a, nullptr, s));

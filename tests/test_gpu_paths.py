@@ -612,3 +612,49 @@ def test_lists_of_long_rows(L, d, b1, b2, ip, M):
             check_topk(metric, pi[i].cpu().numpy(), pd[i].cpu().numpy(), every, ref[c], tol[c], k)
     assert ix.sync() == 0
     ix.close()
+
+
+def test_captured_encode_leaves_the_index_uncaptured(L):
+    """After a captured encode of a batch whose means are found apart, the
+    index is not taken to be capturing: consolidation may allocate, and updates
+    that alternate between streams, with no query between them, wait for each
+    other."""
+    g = synth.rng(8400, 0)
+    n, d, M, m = 20_000, 200, 16, 4096
+    mu = g.standard_normal((M, d)).astype(np.float32)
+    X = (mu[g.integers(0, M, n)] + 0.5 * g.standard_normal((n, d))).astype(np.float32)
+    x = torch.from_numpy(X).cuda()
+    ix = L.Index(d, 8, 0, L.LVQ_L2, L.LVQ_SEQUENTIAL, means=mu, capacity=n)
+    want = ix.encode(x)[0]
+    slots = ix.insert(x)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+
+    def capture():
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=streams[0]):
+            out = ix.encode(x[:m])[0]
+        return graph, out
+
+    torch.cuda.synchronize()
+    graph, out = capture()
+    assert ix.consolidate() == 0          # its scratch and list are allocated here
+    pick = slots[:m].contiguous()
+    torch.cuda.synchronize()
+    for turn in range(4):
+        kept = capture()
+        with torch.cuda.stream(streams[1]):
+            ix.delete(pick)
+        with torch.cuda.stream(streams[2]):
+            assert ix.consolidate() == m
+            back = ix.insert(x[:m])
+        with torch.cuda.stream(streams[1]):
+            rows = ix.read_rows(pick)[0]
+        torch.cuda.synchronize()
+        assert torch.equal(back.sort().values, pick.sort().values)
+        order = back.argsort()[pick.argsort().argsort()]          # row of x that pick's slots hold now
+        assert torch.equal(rows[:, 32:], want[:m][order][:, 32:])
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out, want[:m])
+    assert ix.sync() == 0
+    ix.close()
