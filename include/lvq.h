@@ -20,7 +20,10 @@
  *    the affected outputs, and are reported (and cleared) by lvq_sync.
  *  - The library owns the store (rows, residual rows, means, free-slot list)
  *    and its workspace, all in device memory it allocates itself, counted
- *    against lvq_config.mem_budget_bytes.
+ *    against lvq_config.mem_budget_bytes.  Without a budget, the first
+ *    lvq_encode or lvq_insert of 2,048 or more vectors under several means on
+ *    a stream may allocate 4 MiB for it (the vectors' means, found ahead of the
+ *    encoding); they allocate nothing else and never wait for the device.
  *  - HIP graphs: lvq_distances, lvq_topk, lvq_probe_topk and
  *    lvq_graph_search may be captured into a graph on `stream` once an
  *    uncaptured call of the same size has sized the stream's workspace (a

@@ -589,9 +589,8 @@ static int encode_common(lvq_index *ix, const float *x, int64_t n, uint8_t *rows
     int32_t *buf = nullptr;
     if (encode_assigns(n, ix->f.dim, ix->n_means) && !stream_captures(s) && ix->cfg.mem_budget_bytes <= 0) {
         Workspace &w = workspace(ix, s);
-        size_t room = 4096;   // (doubled, so that growing batches seldom grow the buffer)
-        while ((int64_t)room < std::min<int64_t>(n, kAssignRun)) room *= 2;
-        if (dev_alloc(ix, w.assign, sizeof(int32_t) * room) == LVQ_OK)
+        // (one size for the index's life: growing would wait for the whole device)
+        if (dev_alloc(ix, w.assign, sizeof(int32_t) * (size_t)kAssignRun) == LVQ_OK)
             buf = P<int32_t>(w.assign);
         else
             (void)hipGetLastError();   // the call goes on without it

@@ -658,3 +658,23 @@ def test_captured_encode_leaves_the_index_uncaptured(L):
     assert torch.equal(out, want[:m])
     assert ix.sync() == 0
     ix.close()
+
+
+def test_encode_allocates_once_per_stream(L):
+    """The encoder's buffer of means does not grow with the batch (growing it
+    waits for the device), and is not taken under a memory budget."""
+    n, d, M = 40_000, 192, 16
+    g = synth.rng(8500, 0)
+    mu = g.standard_normal((M, d)).astype(np.float32)
+    x = torch.from_numpy((mu[g.integers(0, M, n)] + 0.5 * g.standard_normal((n, d))).astype(np.float32)).cuda()
+    for budget in (0, 1 << 32):
+        ix = L.Index(d, 8, 0, L.LVQ_L2, L.LVQ_SEQUENTIAL, means=mu, capacity=n, mem_budget_bytes=budget)
+        none = ix.stats().device_bytes
+        want = ix.encode(x[:2048])[0]
+        one = ix.stats().device_bytes
+        assert one - none == (0 if budget else 4 << 20)
+        assert torch.equal(ix.encode(x)[0][:2048], want)
+        ix.insert(x)
+        assert ix.stats().device_bytes == one
+        assert ix.sync() == 0
+        ix.close()
