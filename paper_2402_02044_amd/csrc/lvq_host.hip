@@ -276,14 +276,19 @@ int prep_into(lvq_index *ix, const float *q, int64_t nq, float *qk, float *qsum,
     return LVQ_OK;
 }
 
+// Room for the prepared queries of a batch in the stream's workspace.
+int size_queries(lvq_index *ix, Workspace &w, int64_t nq)
+{
+    int rc;
+    if ((rc = dev_alloc(ix, w.qk, sizeof(float) * (size_t)std::max<int64_t>(nq, 1) * ix->f.kpos))) return rc;
+    if ((rc = dev_alloc(ix, w.qsum, sizeof(float) * (size_t)std::max<int64_t>(nq, 1)))) return rc;
+    return dev_alloc(ix, w.cm, sizeof(float) * (size_t)std::max<int64_t>(nq, 1) * ix->n_means);
+}
+
 int prep_queries(lvq_index *ix, Workspace &w, const float *q, int64_t nq, hipStream_t s)
 {
-    const Format &f = ix->f;
-    int rc;
-    if ((rc = dev_alloc(ix, w.qk, sizeof(float) * (size_t)std::max<int64_t>(nq, 1) * f.kpos))) return rc;
-    if ((rc = dev_alloc(ix, w.qsum, sizeof(float) * (size_t)std::max<int64_t>(nq, 1)))) return rc;
-    if ((rc = dev_alloc(ix, w.cm, sizeof(float) * (size_t)std::max<int64_t>(nq, 1) * ix->n_means))) return rc;
-    return prep_into(ix, q, nq, P<float>(w.qk), P<float>(w.qsum), P<float>(w.cm), s);
+    const int rc = size_queries(ix, w, nq);
+    return rc ? rc : prep_into(ix, q, nq, P<float>(w.qk), P<float>(w.qsum), P<float>(w.cm), s);
 }
 
 // Order of sums of the default tile shape: that of the shape, among those
@@ -803,32 +808,49 @@ int lvq::host_distances(lvq_index *ix, const float *q_dev, int64_t nq, const int
     const int ppb = 4 * (64 / tile_shape(shape).g);
     const double avg = total == INT64_MAX ? (double)ix->list_len * list_nmeans / ix->n_means : (double)total / nq;
     int parts = (int)std::min<double>((double)(slots / nq), avg / (ppb * (1.0 + ntab * f.kpos / 4096)));
+    // The query buffers are sized whatever this call's route is, so that a later
+    // captured call of as many queries finds room (one that does not need them
+    // goes on without).  The keys of split lists follow the prepared queries, or
+    // take their place; the buffer grows for them only where nothing limits it
+    // (no budget, no capture, past or present), and the lists are split into as
+    // many parts as there is room for.
+    const size_t qk_bytes = sizeof(float) * (size_t)nq * f.kpos, keys_at = prep ? (qk_bytes + 255) & ~(size_t)255 : 0;
+    const size_t per_part = sizeof(uint64_t) * (size_t)nq * k;
     Workspace *ws = fixed ? nullptr : &workspace(ix, s);
+    if (ws && (rc = size_queries(ix, *ws, nq))) {
+        if (prep) return rc;
+        (void)hipGetLastError();
+    }
     if (k > 0 && parts > 1) {
-        // room for the keys: the fixed scratch, which prepared queries would
-        // occupy; a workspace that may not grow now keeps the lists whole
-        const size_t need = sizeof(uint64_t) * (size_t)slots * k;
-        if (fixed ? prep || need > fixed->bytes : need > ws->part.bytes && (ix->capturing || ws->part.pinned)) parts = 1;
+        size_t room = fixed ? (prep ? 0 : fixed->bytes) : ws->qk.bytes;
+        const size_t want = keys_at + parts * per_part;
+        if (!fixed && room < want && !ix->capturing && !ws->qk.pinned && ix->cfg.mem_budget_bytes <= 0) {
+            size_t grow = 65536;
+            while (grow < want) grow *= 2;
+            if (dev_alloc(ix, ws->qk, std::max(grow, qk_bytes)) != LVQ_OK) (void)hipGetLastError();
+            room = ws->qk.bytes;
+        }
+        parts = (int)std::min<size_t>(parts, room > keys_at ? (room - keys_at) / per_part : 0);
     }
     parts = std::max(1, parts);
     // every item resident at once: no order, no counter
     const bool queued = nq * parts > slots;
-    prep = prep || (queued && !l2);
+    if (queued && !l2 && !prep) {
+        prep = true;   // (of whole lists: no keys behind the queries)
+        if (ws && (rc = size_queries(ix, *ws, nq))) return rc;
+    }
     DistScratch sc;
     uint64_t *part_keys = nullptr;
     if (fixed) {
         sc = *fixed;
-        part_keys = reinterpret_cast<uint64_t *>(sc.all);
+        if (parts > 1 && k > 0) part_keys = reinterpret_cast<uint64_t *>(sc.all);
         if (prep && (rc = prep_into(ix, q_dev, nq, sc.qk, sc.qsum, sc.cm, s))) return rc;
     } else {
         Workspace &w = *ws;
         if (prep && (rc = prep_queries(ix, w, q_dev, nq, s))) return rc;
         if ((rc = dev_alloc(ix, w.order, sizeof(int32_t) * (size_t)nq))) return rc;
         if ((rc = dev_alloc(ix, w.queue, 64))) return rc;
-        if (parts > 1 && k > 0) {
-            if ((rc = dev_alloc(ix, w.part, sizeof(uint64_t) * (size_t)slots * k))) return rc;
-            part_keys = P<uint64_t>(w.part);
-        }
+        if (parts > 1 && k > 0) part_keys = reinterpret_cast<uint64_t *>(static_cast<char *>(w.qk.p) + keys_at);
         sc = {P<float>(w.qk), P<float>(w.qsum), P<float>(w.cm), P<int32_t>(w.order), P<int32_t>(w.queue), nullptr, 0};
     }
 
@@ -1767,8 +1789,9 @@ int lvq::host_reserve(lvq_index *ix, hipStream_t s, int64_t max_nq, int32_t k_fi
     }
     if (k_rerank > 0) {
         order = sizeof(int32_t) * (size_t)max_nq;
-        // keys of split lists: one item per resident workgroup of 256 lanes
-        part = std::max(part, sizeof(uint64_t) * (size_t)ix->n_cu * 8 * k_rerank);
+        // keys of split lists, behind the queries: at most one item per resident
+        // workgroup of 256 lanes (host_distances takes no room for them under a budget)
+        if (ix->cfg.mem_budget_bytes <= 0) qk += 256 + sizeof(uint64_t) * (size_t)ix->n_cu * 8 * k_rerank;
     }
     Workspace &w = workspace(ix, s);
     int rc;

@@ -678,3 +678,44 @@ def test_encode_allocates_once_per_stream(L):
         assert ix.stats().device_bytes == one
         assert ix.sync() == 0
         ix.close()
+
+
+@pytest.mark.parametrize("ip,M", [(0, 1), (1, 1), (1, 40), (0, 5)])
+def test_split_lists_within_a_budget(L, ip, M):
+    """Short batches whose lists would be split are not refused under a memory
+    budget with room for the queries alone, nor does the splitting take room
+    that a later call needs; values are those without a budget."""
+    g = synth.rng(8600 + M, ip)
+    n, d = 5000, 96
+    X = g.standard_normal((n, d)).astype(np.float32)
+    means = (X[:M] * 0.4).astype(np.float32)
+    x = torch.from_numpy(X).cuda()
+    metric = L.LVQ_IP if ip else L.LVQ_L2
+    q = torch.from_numpy(g.standard_normal((3, d)).astype(np.float32)).cuda()
+    offs = torch.tensor([0, 4000, 4001, 9000], device="cuda")
+    ids = torch.from_numpy(g.integers(0, n, 9000).astype(np.int32)).cuda()
+    free = L.Index(d, 8, 0, metric, L.LVQ_SEQUENTIAL, capacity=n, means=means)
+    free.insert(x)
+    base = free.stats().device_bytes
+    room = 3 * (d + 1 + M) * 4 + 3 * 4 + 64          # queries, their sums and mean terms, order, counter
+    calls = [lambda i: i.distances(q, offs, ids, k=200), lambda i: i.distances(q, offs, ids, k=1000)]
+    want = [c(free) for c in calls]
+    tight = L.Index(d, 8, 0, metric, L.LVQ_SEQUENTIAL, capacity=n, means=means, mem_budget_bytes=base + room)
+    tight.insert(x)
+    for c, w in zip(calls, want):
+        for a, b in zip(c(tight), w):
+            assert torch.equal(a, b)
+    assert tight.stats().device_bytes <= base + room
+    used = free.stats().device_bytes - base          # grown for the parts in use, not for every workgroup
+    assert used < (1 << 20) + 8 * 1000 * (3 * 64) * 2
+    # the probe: its member lists as well
+    probe = lambda i: i.probe_topk(q, 1, 300)
+    w = probe(free)
+    more = base + 4 * n + 8 * 257 + 2 * 8 * 256 + 8 * 4 + 3 * 4 + room + 4 * 64
+    tight2 = L.Index(d, 8, 0, metric, L.LVQ_SEQUENTIAL, capacity=n, means=means, mem_budget_bytes=more)
+    tight2.insert(x)
+    for a, b in zip(probe(tight2), w):
+        assert torch.equal(a, b)
+    for i in (free, tight, tight2):
+        assert i.sync() == 0
+        i.close()
