@@ -272,28 +272,38 @@ __global__ void k_delete(StoreArgs a, const int32_t *slots, int64_t n)
 // take 19 us, 64 MB of sectors) and keeps what the others need as a bit per slot: reclaimable
 // (tombstoned at an epoch no running query precedes) and still occupied; it
 // counts both per block of 1024 slots.  (Four passes over the headers before:
-// 76 us, 35 us now with the scan and the writes.)
+// 76 us, 35 us now with the scan and the writes.)  Where there is no room for
+// the bits (a memory budget), the passes run twice over the headers, for the
+// reclaimable and then for the occupied, with one count per block in all.
 struct SlotBits {
-    uint64_t *gone, *kept;        // a word per 64 slots
-    int32_t *n_gone, *n_kept;     // a count per 1024
+    uint64_t *gone, *kept;        // a word per 64 slots; NULL: not kept
+    int32_t *n_gone, *n_kept;     // a count per 1024; NULL: the other round's
 };
 
-__global__ __launch_bounds__(1024) void k_consolidate_count(StoreArgs a, uint32_t safe_epoch, SlotBits b)
+__device__ __forceinline__ void slot_state(const StoreArgs &a, int64_t s, uint32_t safe_epoch, bool *gone, bool *kept)
 {
-    __shared__ int wsum[2][16];
-    const int64_t s = (int64_t)blockIdx.x * 1024 + threadIdx.x;
-    bool used = false, gone = false;
+    bool used = false;
+    *gone = false;
     if (s < a.capacity) {
         const uint8_t *row = a.rows + s * a.row_bytes;
         const uint32_t w = *reinterpret_cast<const uint32_t *>(row + 12);   // mean id, flags
         const uint32_t del = *reinterpret_cast<const uint32_t *>(row + 20);
         used = (w >> 8) & 1u;
-        gone = used && del != kLiveEpoch && del <= safe_epoch;
+        *gone = used && del != kLiveEpoch && del <= safe_epoch;
     }
-    const uint64_t mg = __ballot(gone), mk = __ballot(used && !gone);
+    *kept = used && !*gone;
+}
+
+__global__ __launch_bounds__(1024) void k_consolidate_count(StoreArgs a, uint32_t safe_epoch, SlotBits b)
+{
+    __shared__ int wsum[2][16];
+    const int64_t s = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+    bool gone, kept;
+    slot_state(a, s, safe_epoch, &gone, &kept);
+    const uint64_t mg = __ballot(gone), mk = __ballot(kept);
     if ((threadIdx.x & 63) == 0) {
         const int w = threadIdx.x >> 6;
-        if (s < a.capacity) {
+        if (b.gone && s < a.capacity) {
             b.gone[s >> 6] = mg;
             b.kept[s >> 6] = mk;
         }
@@ -304,7 +314,8 @@ __global__ __launch_bounds__(1024) void k_consolidate_count(StoreArgs a, uint32_
     if (threadIdx.x < 2) {
         int t = 0;
         for (int w = 0; w < 16; ++w) t += wsum[threadIdx.x][w];
-        (threadIdx.x == 0 ? b.n_gone : b.n_kept)[blockIdx.x] = t;
+        int32_t *n = threadIdx.x == 0 ? b.n_gone : b.n_kept;
+        if (n) n[blockIdx.x] = t;
     }
 }
 
@@ -348,33 +359,59 @@ __device__ int64_t block_exclusive_scan(int32_t *counts, int nb, bool descending
 __global__ __launch_bounds__(1024) void k_consolidate_scan(SlotBits b, int nblocks, int64_t free_top, int64_t *out)
 {
     const bool gone = blockIdx.x == 0;
-    const int64_t total = block_exclusive_scan(gone ? b.n_gone : b.n_kept, nblocks, gone);
+    int32_t *n = gone ? b.n_gone : b.n_kept;
+    if (!n) return;
+    const int64_t total = block_exclusive_scan(n, nblocks, gone);
     if (threadIdx.x == 0) out[blockIdx.x] = gone ? free_top + total : total;
 }
 
 // pass 3: push the reclaimable slots (descending slot order) and clear their
 // headers; write the occupied ones in ascending order
-__global__ __launch_bounds__(1024) void k_consolidate_write(StoreArgs a, SlotBits b, int32_t *stack, int64_t free_top,
-                                                            int32_t *list)
+template <bool BITS>
+__global__ __launch_bounds__(1024) void k_consolidate_write(StoreArgs a, uint32_t safe_epoch, SlotBits b, int32_t *stack,
+                                                            int64_t free_top, int32_t *list)
 {
     const int64_t s = (int64_t)blockIdx.x * 1024 + threadIdx.x;
-    if (s >= a.capacity) return;
-    const int64_t w0 = (int64_t)blockIdx.x * 16, w = s >> 6, words = (a.capacity + 63) >> 6;
     const int lane = threadIdx.x & 63;
-    const uint64_t mg = b.gone[w], mk = b.kept[w];
-    if (!(mg | mk)) return;
-    int above = __popcll(lane == 63 ? 0ull : mg >> (lane + 1)), below = __popcll(mk & ((1ull << lane) - 1ull));
-    for (int64_t v = w0; v < min(words, w0 + 16); ++v) {
-        if (v > w) above += __popcll(b.gone[v]);
-        if (v < w) below += __popcll(b.kept[v]);
+    uint64_t mg, mk;
+    int above = 0, below = 0;   // in the block's other waves
+    if constexpr (BITS) {
+        if (s >= a.capacity) return;
+        const int64_t w0 = (int64_t)blockIdx.x * 16, w = s >> 6, words = (a.capacity + 63) >> 6;
+        mg = b.gone[w];
+        mk = b.kept[w];
+        if (!(mg | mk)) return;
+        for (int64_t v = w0; v < min(words, w0 + 16); ++v) {
+            if (v > w) above += __popcll(b.gone[v]);
+            if (v < w) below += __popcll(b.kept[v]);
+        }
+    } else {
+        __shared__ int wsum[2][16];
+        const int wave = threadIdx.x >> 6;
+        bool gone, kept;
+        slot_state(a, s, safe_epoch, &gone, &kept);
+        mg = __ballot(gone);
+        mk = __ballot(kept);
+        if (lane == 0) {
+            wsum[0][wave] = __popcll(mg);
+            wsum[1][wave] = __popcll(mk);
+        }
+        __syncthreads();
+        if (s >= a.capacity) return;
+        for (int w = 0; w < 16; ++w) {
+            if (w > wave) above += wsum[0][w];
+            if (w < wave) below += wsum[1][w];
+        }
     }
-    if ((mg >> lane) & 1) {
+    above += __popcll(lane == 63 ? 0ull : mg >> (lane + 1));
+    below += __popcll(mk & ((1ull << lane) - 1ull));
+    if (b.n_gone && ((mg >> lane) & 1)) {
         stack[free_top + b.n_gone[blockIdx.x] + above] = (int32_t)s;
         uint4 *h = reinterpret_cast<uint4 *>(a.rows + s * a.row_bytes);
         h[0] = make_uint4(0u, 0u, 0u, 0u);
         h[1] = make_uint4(0u, 0u, 0u, 0u);
     }
-    if ((mk >> lane) & 1) list[b.n_kept[blockIdx.x] + below] = (int32_t)s;
+    if (b.n_kept && ((mk >> lane) & 1)) list[b.n_kept[blockIdx.x] + below] = (int32_t)s;
 }
 
 __global__ void k_gather_rows(StoreArgs a, const int32_t *slots, int64_t n, uint8_t *rows_out,
@@ -632,27 +669,36 @@ hipError_t launch_delete(const StoreArgs &a, const int32_t *slots, int64_t n, hi
     return hipGetLastError();
 }
 
-size_t consolidate_scratch(int64_t capacity)
+size_t consolidate_scratch(int64_t capacity, bool bits)
 {
     const size_t words = (size_t)(capacity + 63) / 64, nb = (size_t)(capacity + 1023) / 1024;
-    return 2 * words * sizeof(uint64_t) + 2 * nb * sizeof(int32_t);
+    return bits ? 2 * words * sizeof(uint64_t) + 2 * nb * sizeof(int32_t) : nb * sizeof(int32_t);
 }
 
 hipError_t launch_consolidate(const StoreArgs &a, uint32_t safe_epoch, int32_t *free_stack, int64_t free_top,
-                              int32_t *list, void *scratch, int64_t *out, hipStream_t s)
+                              int32_t *list, void *scratch, bool bits, int64_t *out, hipStream_t s)
 {
     const int nb = (int)((a.capacity + 1023) / 1024);
     if (nb == 0) return hipSuccess;
-    const size_t words = (size_t)(a.capacity + 63) / 64;
-    SlotBits b;
-    b.gone = reinterpret_cast<uint64_t *>(scratch);
-    b.kept = b.gone + words;
-    b.n_gone = reinterpret_cast<int32_t *>(b.kept + words);
-    b.n_kept = b.n_gone + nb;
-    hipLaunchKernelGGL(k_consolidate_count, dim3(nb), dim3(1024), 0, s, a, safe_epoch, b);
-    hipLaunchKernelGGL(k_consolidate_scan, dim3(2), dim3(1024), 0, s, b, nb, free_top, out);
-    hipLaunchKernelGGL(k_consolidate_write, dim3(nb), dim3(1024), 0, s, a, b, free_stack, free_top, list);
-    return hipGetLastError();
+    auto passes = [&](const SlotBits &b) {
+        hipLaunchKernelGGL(k_consolidate_count, dim3(nb), dim3(1024), 0, s, a, safe_epoch, b);
+        hipLaunchKernelGGL(k_consolidate_scan, dim3(2), dim3(1024), 0, s, b, nb, free_top, out);
+        hipLaunchKernelGGL(b.gone ? k_consolidate_write<true> : k_consolidate_write<false>, dim3(nb), dim3(1024), 0, s,
+                           a, safe_epoch, b, free_stack, free_top, list);
+        return hipGetLastError();
+    };
+    if (bits) {
+        const size_t words = (size_t)(a.capacity + 63) / 64;
+        SlotBits b;
+        b.gone = reinterpret_cast<uint64_t *>(scratch);
+        b.kept = b.gone + words;
+        b.n_gone = reinterpret_cast<int32_t *>(b.kept + words);
+        b.n_kept = b.n_gone + nb;
+        return passes(b);
+    }
+    int32_t *counts = reinterpret_cast<int32_t *>(scratch);
+    const hipError_t e = passes({nullptr, nullptr, counts, nullptr});
+    return e != hipSuccess ? e : passes({nullptr, nullptr, nullptr, counts});
 }
 
 hipError_t launch_gather_rows(const StoreArgs &a, const int32_t *slots, int64_t n, uint8_t *rows_out,

@@ -511,7 +511,7 @@ int lvq_destroy(lvq_index *ix)
             dev_free(ix, *b);
     }
     for (DevBuf *b : {&ix->means, &ix->means_t, &ix->muk, &ix->kmask, &ix->kdim, &ix->rows,
-                      &ix->resid, &ix->stack, &ix->err, &ix->scratch, &ix->mean_active, &ix->mean_counts})
+                      &ix->resid, &ix->stack, &ix->err, &ix->scratch, &ix->slot_bits, &ix->mean_active, &ix->mean_counts})
         dev_free(ix, *b);
     for (SlotList &l : ix->lists) dev_free(ix, l.buf);
     for (auto &f : ix->inflight) (void)hipEventDestroy(f.ev);
@@ -714,11 +714,23 @@ int lvq_consolidate(lvq_index *ix, void *stream, int64_t *n_freed_out)
         ix->lists.push_back(fresh_list);
         next = (int)ix->lists.size() - 1;
     }
-    const size_t bits = consolidate_scratch(cap), tail_at = (bits + 15) & ~(size_t)15;
-    if ((rc = dev_alloc(ix, ix->scratch, tail_at + 16))) return rc;
-    int64_t *tail = reinterpret_cast<int64_t *>(reinterpret_cast<char *>(ix->scratch.p) + tail_at);
+    // Room for a bit per slot, in a buffer of its own that never grows (growing
+    // one waits for the device); not taken from a memory budget, nor where the
+    // allocation fails: then the passes keep a count per block alone.
+    auto up16 = [](size_t b) { return (b + 15) & ~(size_t)15; };
+    size_t tail_at = up16(consolidate_scratch(cap, true));
+    DevBuf *mem = ix->scratch.bytes >= tail_at + 16 ? &ix->scratch : &ix->slot_bits;
+    if (mem == &ix->slot_bits && !mem->p && ix->cfg.mem_budget_bytes <= 0 && dev_alloc(ix, *mem, tail_at + 16) != LVQ_OK)
+        (void)hipGetLastError();
+    const bool bits = mem->p != nullptr;
+    if (!bits) {
+        mem = &ix->scratch;
+        tail_at = up16(consolidate_scratch(cap, false));
+        if ((rc = dev_alloc(ix, *mem, tail_at + 16))) return rc;
+    }
+    int64_t *tail = reinterpret_cast<int64_t *>(static_cast<char *>(mem->p) + tail_at);
     LVQ_HIP(launch_consolidate(store_args(ix), safe, P<int32_t>(ix->stack), ix->free_top,
-                               P<int32_t>(ix->lists[next].buf), ix->scratch.p, tail, s));
+                               P<int32_t>(ix->lists[next].buf), mem->p, bits, tail, s));
     int64_t got[2] = {0, 0};   // new stack top, list length
     LVQ_HIP(hipMemcpyAsync(got, tail, sizeof(got), hipMemcpyDeviceToHost, s));
     LVQ_HIP(hipStreamSynchronize(s));

@@ -337,10 +337,10 @@ hipError_t launch_delete(const StoreArgs &a, const int32_t *slots, int64_t n, hi
 // Reclaim the slots tombstoned at or before safe_epoch (pushed on the stack,
 // headers cleared) and list the occupied ones, ascending, into list; out[0]: the
 // new stack top, out[1]: the list's length.  scratch: consolidate_scratch
-// bytes, 8-byte aligned.
-size_t consolidate_scratch(int64_t capacity);
+// bytes, 8-byte aligned; bits: with room for a bit per slot.
+size_t consolidate_scratch(int64_t capacity, bool bits);
 hipError_t launch_consolidate(const StoreArgs &a, uint32_t safe_epoch, int32_t *free_stack, int64_t free_top,
-                              int32_t *list, void *scratch, int64_t *out, hipStream_t s);
+                              int32_t *list, void *scratch, bool bits, int64_t *out, hipStream_t s);
 hipError_t launch_gather_rows(const StoreArgs &a, const int32_t *slots, int64_t n, uint8_t *rows_out,
                               uint8_t *resid_out, hipStream_t s);
 hipError_t launch_mean(const float *x, int64_t n, int dim, float *out, double *scratch, hipStream_t s);

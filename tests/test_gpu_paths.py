@@ -719,3 +719,54 @@ def test_split_lists_within_a_budget(L, ip, M):
     for i in (free, tight, tight2):
         assert i.sync() == 0
         i.close()
+
+
+@pytest.mark.parametrize("cap", [1, 1024, 1025, 30_000])
+def test_consolidation_within_a_budget(L, cap):
+    """Consolidation under a memory budget that holds the store and its second
+    slot list alone frees the same slots in the same order, and leaves the same
+    list, as without one."""
+    g = synth.rng(8700 + cap, 0)
+    d = 32
+    X = torch.from_numpy(int_rows(g, max(cap, 2), d)[:cap]).cuda()
+    means = np.zeros((1, d), np.float32)
+    free = L.Index(d, 8, 0, L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=cap, means=means)
+    tight = L.Index(d, 8, 0, L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=cap, means=means,
+                    mem_budget_bytes=free.stats().device_bytes + 4 * cap)
+    dead = torch.from_numpy(np.unique(g.integers(0, cap, max(1, cap // 3))).astype(np.int32)).cuda()
+    for turn in range(3):
+        took = []
+        for ix in (free, tight):
+            if turn == 0:
+                ix.insert(X)
+            ix.delete(dead)
+            assert ix.consolidate() == len(dead) and ix.consolidate() == 0
+            if turn == 1:
+                continue      # the freed slots stay free for a turn
+            took.append(ix.insert(X[:len(dead)]))
+        if turn == 1:
+            took = [ix.insert(X[:len(dead)]) for ix in (free, tight)]
+        assert torch.equal(took[0], took[1])
+        every = torch.arange(cap, dtype=torch.int32, device="cuda")
+        assert torch.equal(free.read_rows(every)[0], tight.read_rows(every)[0])
+    k = min(50, cap)
+    free.delete(dead[:3])
+    tight.delete(dead[:3])
+    assert free.consolidate() == tight.consolidate()
+    big = L.Index(d, 8, 0, L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=cap, means=means, mem_budget_bytes=1 << 32)
+    big.insert(X)
+    big.delete(dead)
+    assert big.consolidate() == len(dead)
+    live = np.setdiff1d(np.arange(cap), dead.cpu().numpy())
+    if len(live):
+        Q = int_queries(g, 2, d)
+        v = np.full((2, cap), np.inf)
+        v[:, live] = values(False, Q, X.cpu().numpy()[live])
+        ids, val = best(False, v, k)
+        ids[~np.isfinite(val)] = -1
+        ti, td = big.topk(torch.from_numpy(Q).cuda(), k)      # walks the list of occupied slots
+        np.testing.assert_array_equal(ti.cpu().numpy(), ids)
+        np.testing.assert_array_equal(td.cpu().numpy().astype(np.float64), val)
+    for ix in (free, tight, big):
+        assert ix.sync() == 0
+        ix.close()
