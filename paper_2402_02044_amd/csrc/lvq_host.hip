@@ -276,13 +276,27 @@ int prep_into(lvq_index *ix, const float *q, int64_t nq, float *qk, float *qsum,
     return LVQ_OK;
 }
 
-// Room for the prepared queries of a batch in the stream's workspace.
+// Bytes of the vector scan's query table, in tiles of tq queries, and of the
+// queries' shared bounds behind it (both in Workspace::qk).
+size_t scan_table_bytes(const lvq_index *ix, int64_t nq, int tq)
+{
+    return sizeof(float) * (size_t)((nq + tq - 1) / tq * tq * ix->f.kpos + nq);
+}
+
+// Room for the prepared queries of a batch in the stream's workspace (without a
+// budget, for a scan of as many queries in tiles of 16 too: after a capture it
+// cannot grow).
 int size_queries(lvq_index *ix, Workspace &w, int64_t nq)
 {
-    int rc;
-    if ((rc = dev_alloc(ix, w.qk, sizeof(float) * (size_t)std::max<int64_t>(nq, 1) * ix->f.kpos))) return rc;
-    if ((rc = dev_alloc(ix, w.qsum, sizeof(float) * (size_t)std::max<int64_t>(nq, 1)))) return rc;
-    return dev_alloc(ix, w.cm, sizeof(float) * (size_t)std::max<int64_t>(nq, 1) * ix->n_means);
+    nq = std::max<int64_t>(nq, 1);
+    const size_t exact = sizeof(float) * (size_t)nq * ix->f.kpos;
+    int rc = LVQ_ERR_OOM;
+    if (w.qk.bytes < exact && !ix->capturing && !w.qk.pinned && ix->cfg.mem_budget_bytes <= 0 &&
+        (rc = dev_alloc(ix, w.qk, scan_table_bytes(ix, nq, 16))))
+        (void)hipGetLastError();
+    if (rc && (rc = dev_alloc(ix, w.qk, exact))) return rc;
+    if ((rc = dev_alloc(ix, w.qsum, sizeof(float) * (size_t)nq))) return rc;
+    return dev_alloc(ix, w.cm, sizeof(float) * (size_t)nq * ix->n_means);
 }
 
 int prep_queries(lvq_index *ix, Workspace &w, const float *q, int64_t nq, hipStream_t s)
@@ -1066,7 +1080,7 @@ static bool scan_plan_pairs(const lvq_index *ix, int64_t nq, int32_t k, int32_t 
     return true;
 }
 
-static bool scan_plan(const lvq_index *ix, int64_t nq, int32_t k, int32_t level, ScanPlan *p)
+static bool scan_plan(const lvq_index *ix, int64_t nq, int32_t k, int32_t level, ScanPlan *p, bool few_only = false)
 {
     const Format &f = ix->f;
     const bool l2 = ix->cfg.metric == LVQ_L2;
@@ -1094,7 +1108,7 @@ static bool scan_plan(const lvq_index *ix, int64_t nq, int32_t k, int32_t level,
     // lists too long for a full tile's LDS
     const int g = tile_shape(shape).g, ch = tile_shape(shape).ch;
     const int full = scan_tile_queries(g, ch, f.bits1, false);
-    const bool few = 2 * nq <= full || scan_lds_bytes(full, nm, k, g, f.bits1, bits2) > ix->lds_max;
+    const bool few = few_only || 2 * nq <= full || scan_lds_bytes(full, nm, k, g, f.bits1, bits2) > ix->lds_max;
     p->tq = scan_tile_queries(g, ch, f.bits1, few);
     p->lds = scan_lds_bytes(p->tq, nm, k, g, f.bits1, bits2);
     if (p->lds > ix->lds_max) return false;
@@ -1116,12 +1130,21 @@ static bool scan_plan(const lvq_index *ix, int64_t nq, int32_t k, int32_t level,
 // 300,000 rows 55 us with 256 parts, 67 with 512, 117 with 1,024; 4x8 d = 768 204,
 // 182 and 223 us.  Parts of at least one round, and at most 20,480 keys to
 // merge per query.
+//
+// Under a memory budget no more than four workgroups of sixteen queries per
+// unit and 1,024 rows per part: the keys are charged to the budget, and the
+// counts above can ask for 16 times as many (nq x parts x k keys).
 static int64_t scan_parts_fp32(const lvq_index *ix, const ScanPlan &pl, int64_t nq, int32_t k, int64_t n_rows)
 {
     const double merge = (k <= 64 ? 0.25 : 0.1) * k * 96.0 / ix->f.kpos;
     const int64_t qtiles = (nq + pl.tq - 1) / pl.tq, occ = std::max<int64_t>(1, pl.slots / ix->n_cu);
-    const int64_t most = std::max<int64_t>(1, std::min<int64_t>({n_rows / 256, (int64_t)(ix->lds_max / 8 - k) / k,
-                                                                 2 * pl.slots / qtiles + 1}));
+    int64_t most = std::max<int64_t>(1, std::min<int64_t>({n_rows / 256, (int64_t)(ix->lds_max / 8 - k) / k,
+                                                           2 * pl.slots / qtiles + 1}));
+    if (ix->cfg.mem_budget_bytes > 0) {
+        const int64_t tiles16 = (nq + 15) / 16;
+        most = std::min(most, std::max<int64_t>(1, std::min<int64_t>((4 * (int64_t)ix->n_cu + tiles16 - 1) / tiles16,
+                                                                     n_rows / 1024)));
+    }
     auto shared = [](int64_t c) { return (double)c * (c == 1 ? 1.77 : c == 2 ? 1.14 : 1.0); };
     int64_t parts = 1;
     double best = 0.0;
@@ -1284,18 +1307,34 @@ int lvq::host_topk(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq, i
     int rc = order_after_updates(ix, s);
     if (rc) return rc;
     Workspace &w = workspace(ix, s);
+    // Where the workspace has no room and cannot grow (a capture, a budget): the
+    // smallest tiles, or for few inner products the matrix cores; and the row
+    // parts whose keys there is room for.
+    if ((rc = dev_alloc(ix, w.qk, scan_table_bytes(ix, nq, pl.tq)))) {
+        (void)hipGetLastError();
+        if (pl.pair_chunk) return topk_mfma(ix, q_dev, LVQ_FP32, nq, k, level, ids_dev, dist_dev, s, epoch);
+        if (!scan_plan(ix, nq, k, level, &pl, true)) return rc;
+        if ((rc = dev_alloc(ix, w.qk, scan_table_bytes(ix, nq, pl.tq)))) return rc;
+    }
     const int tq = pl.tq;
     const int64_t qtiles = (nq + tq - 1) / tq;
     const int64_t n_rows = ix->list_len;
-    const int64_t parts = scan_parts_fp32(ix, pl, nq, k, n_rows);
+    int64_t parts = scan_parts_fp32(ix, pl, nq, k, n_rows);
+    if (!l2) {   // (Euclidean scans use neither)
+        if ((rc = dev_alloc(ix, w.qsum, sizeof(float) * (size_t)nq))) return rc;
+        if ((rc = dev_alloc(ix, w.cm, sizeof(float) * (size_t)nq * ix->n_means))) return rc;
+    }
+    const size_t per_part = sizeof(uint64_t) * (size_t)nq * k;
+    while ((rc = dev_alloc(ix, w.part, per_part * parts))) {
+        if (parts == 1) return rc;
+        (void)hipGetLastError();
+        // what the buffer has now, or half as many
+        parts = std::max<int64_t>(1, std::max<int64_t>(parts / 2, std::min<int64_t>(parts - 1, w.part.bytes / per_part)));
+    }
     const int64_t rows_per_part = std::max<int64_t>(1, (n_rows + parts - 1) / parts);
-    if ((rc = dev_alloc(ix, w.qk, sizeof(float) * (size_t)qtiles * tq * f.kpos))) return rc;
-    if ((rc = dev_alloc(ix, w.qsum, sizeof(float) * (size_t)nq))) return rc;
-    if ((rc = dev_alloc(ix, w.cm, sizeof(float) * (size_t)nq * ix->n_means))) return rc;
-    if ((rc = dev_alloc(ix, w.gthr, sizeof(uint32_t) * (size_t)nq))) return rc;
-    if ((rc = dev_alloc(ix, w.part, sizeof(uint64_t) * (size_t)nq * parts * k))) return rc;
+    uint32_t *bounds = reinterpret_cast<uint32_t *>(P<float>(w.qk) + qtiles * tq * f.kpos);
     LVQ_HIP(launch_prep_rows(prep_args(ix, (const float *)q_dev, nq, P<float>(w.qk), P<float>(w.qsum), P<float>(w.cm)),
-                             P<float>(ix->muk), tq, pl.pair_chunk, P<uint32_t>(w.gthr), s));
+                             P<float>(ix->muk), tq, pl.pair_chunk, bounds, s));
 
     ScanArgs a;
     a.rows = P<uint8_t>(ix->rows);
@@ -1319,7 +1358,7 @@ int lvq::host_topk(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq, i
     a.rows_per_part = rows_per_part;
     a.n_parts = (int)parts;
     a.capq = 0;
-    a.gthr = P<uint32_t>(w.gthr);
+    a.gthr = bounds;
     a.part_keys = P<uint64_t>(w.part);
     a.err = P<uint32_t>(ix->err);
     a.mks = scan_sorted_keys(k);
@@ -1729,7 +1768,8 @@ int lvq::host_reserve(lvq_index *ix, hipStream_t s, int64_t max_nq, int32_t k_fi
     size_t qk = 0, part = 0, q16 = 0, gthr = 0, order = 0, mkeys = 0;
     const size_t qsum = sizeof(float) * (size_t)max_nq;
     const size_t cm = sizeof(float) * (size_t)max_nq * kMaxMeans;   // any mean count the index may reach
-    if (prec == LVQ_FP32 || k_rerank > 0) qk = sizeof(float) * (size_t)((max_nq + 15) / 16 * 16) * f.kpos;
+    if (prec == LVQ_FP32) qk = scan_table_bytes(ix, max_nq, 16);
+    else if (k_rerank > 0) qk = sizeof(float) * (size_t)max_nq * f.kpos;
     // the wide matrix-core scan, at the most queries of every tile count; with
     // a sample its part count does not only grow with the rows, so fewer are
     // looked at too
@@ -1749,16 +1789,20 @@ int lvq::host_reserve(lvq_index *ix, hipStream_t s, int64_t max_nq, int32_t k_fi
         }
     };
     if (prec == LVQ_FP32) {
-        gthr = sizeof(uint32_t) * (size_t)max_nq;
-        // (the vector scan's tile size changes once with the batch size)
+        // the vector scans, over fewer rows too: their part counts do not only grow
+        // with the rows (under a budget they do, nearly).  The tile size changes
+        // once with the batch size, up to 9 queries.
         ScanPlan pl, pp;
         bool have = false;
         for (int64_t nq = 1; nq <= max_nq; ++nq) {
             if (nq <= 9) have = scan_plan(ix, nq, k_first, scan_level, &pl);
-            if (scan_plan_pairs(ix, nq, k_first, scan_level, &pp))
-                part = std::max(part, sizeof(uint64_t) * (size_t)(nq * scan_parts_fp32(ix, pp, nq, k_first, n_rows) * k_first));
-            if (have)
-                part = std::max(part, sizeof(uint64_t) * (size_t)(nq * scan_parts_fp32(ix, pl, nq, k_first, n_rows) * k_first));
+            const bool pairs = scan_plan_pairs(ix, nq, k_first, scan_level, &pp);
+            for (int64_t rows = n_rows; have || pairs; rows = rows * 7 / 8) {
+                int64_t parts = have ? scan_parts_fp32(ix, pl, nq, k_first, rows) : 0;
+                if (pairs) parts = std::max(parts, scan_parts_fp32(ix, pp, nq, k_first, rows));
+                part = std::max(part, sizeof(uint64_t) * (size_t)(nq * parts * k_first));
+                if (rows <= 512 || ix->cfg.mem_budget_bytes > 0) break;
+            }
         }
         // the FP32 matrix-core scan (inner product; its query block does not
         // depend on the mean count, which only decides whether the c_m table
@@ -1769,6 +1813,7 @@ int lvq::host_reserve(lvq_index *ix, hipStream_t s, int64_t max_nq, int32_t k_fi
                             : 0;
         if (qbf) {
             const int64_t tq = 32 * qbf;
+            gthr = sizeof(uint32_t) * (size_t)max_nq;
             q16 = (size_t)((max_nq + tq - 1) / tq) * tq * f.kpos * 4;
             reserve_wide(tq, scan_level == LVQ_FULL ? f.bits2 : 0);
         }

@@ -31,8 +31,8 @@ struct DistScratch {
     size_t bytes;    //   (which use nothing else of it)
 };
 
-// Per-stream scratch of the query entry points.  (qk also holds the keys of
-// split candidate lists.)
+// Per-stream scratch of the query entry points.  (qk also holds the vector
+// scan's query table with its bounds, and the keys of split candidate lists.)
 struct Workspace {
     DevBuf qk, qsum, cm, order, queue, part, q16, gthr, mkeys;
     // soft inverted index: this stream's per-mean member lists (built at

@@ -770,3 +770,76 @@ def test_consolidation_within_a_budget(L, cap):
     for ix in (free, tight, big):
         assert ix.sync() == 0
         ix.close()
+
+
+@pytest.mark.parametrize("ip", [0, 1])
+@pytest.mark.parametrize("nq,k", [(1, 50), (9, 20), (16, 100), (33, 3)])
+def test_vector_scan_within_a_budget(L, ip, nq, k):
+    """FP32 scans under a memory budget that holds the store, the queries and the
+    keys of the parts of 1,024 rows: not refused for the keys of more parts, and
+    the results are those without a budget."""
+    g = synth.rng(8800 + nq, k + ip)
+    n, d = 6000, 96
+    X, Q = int_rows(g, n, d), int_queries(g, nq, d)
+    ids, val = best(ip, values(ip, Q, X).astype(np.float64), k)
+    base = L.Index(d, 8, 0, L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=n, means=np.zeros((1, d), np.float32))
+    room = base.stats().device_bytes + nq * (4 * d + 8) + 8 * nq * 5 * k
+    base.close()
+    ix = L.Index(d, 8, 0, L.LVQ_IP if ip else L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=n,
+                 means=np.zeros((1, d), np.float32), mem_budget_bytes=room)
+    ix.insert(torch.from_numpy(X).cuda())
+    ti, td = ix.topk(torch.from_numpy(Q).cuda(), k, plain=bool(ip))
+    assert ix.sync() == 0 and ix.stats().device_bytes <= room
+    np.testing.assert_array_equal(ti.cpu().numpy(), ids)
+    np.testing.assert_array_equal(td.cpu().numpy().astype(np.float64), val)
+    ix.close()
+
+
+def test_vector_scan_in_a_fixed_workspace(L):
+    """FP32 scans on a stream whose workspace a capture has fixed at the size of
+    the same batch's lists, and a captured scan of fewer queries than the call
+    that sized the workspace, which ran on the matrix cores."""
+    g = synth.rng(8900, 0)
+    n, d, nq, M = 5000, 96, 10, 20
+    X, Q = int_rows(g, n, d), int_queries(g, nq, d)
+    means = np.zeros((M, d), np.float32)
+    ix = store(L, X, True, means=means)
+    q, q20 = torch.from_numpy(Q).cuda(), torch.from_numpy(int_queries(g, 20, d)).cuda()
+    offs = torch.arange(nq + 1, device="cuda") * 30
+    ids = torch.from_numpy(g.integers(0, n, 30 * nq).astype(np.int32)).cuda()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        ix.distances(q, offs, ids, k=5)
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        lists = ix.distances(q, offs, ids, k=5)
+    want = best(True, values(True, Q, X).astype(np.float64), 7)
+    with torch.cuda.stream(s):
+        got = ix.topk(q, 7, plain=True)
+    s.synchronize()
+    np.testing.assert_array_equal(got[0].cpu().numpy(), want[0])
+    np.testing.assert_array_equal(got[1].cpu().numpy().astype(np.float64), want[1])
+    ref = ix.distances(q, offs, ids, k=5)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(lists, ref):
+            assert torch.equal(a, b)
+    for warm in (20, 5):       # matrix cores; the vector scan
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            ix.topk(q20[:warm], 7)
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            got = ix.topk(q[:5], 7)
+        for _ in range(3):
+            for t in got:
+                t.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(got[0].cpu().numpy(), want[0][:5])
+            np.testing.assert_array_equal(got[1].cpu().numpy().astype(np.float64), want[1][:5])
+    assert ix.sync() == 0
+    ix.close()
