@@ -507,8 +507,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
             const int t = i / a.kpos, sp = i - t * a.kpos;
             mutab[(size_t)t * a.kpos + qtab_index<B1, CH>(sp, npieces)] = a.muk[i];
         }
+    // What only a workgroup of one item needs (its part; the query and means of
+    // an inner product) is read from the argument segment where it is used, and the set-up's addresses are
+    // made anew for every item: kept for the whole kernel they cost a wave (4x4
+    // IP in 16 lanes 175 registers, 160 so: two waves per SIMD, three; 600 lists
+    // of 3,000 at d = 1536 1,451 us, 639).  A workgroup of many items does not
+    // read the segment again, which lies in host memory (every argument of every
+    // item read there: 1,100 ragged lists at 8-bit d = 512 114 us, 131).
+    auto more_args = []() {
+        auto p = (const __attribute__((address_space(4))) CandArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(p));
+        return p;
+    };
     for (int iter = 0;; ++iter) {
-        int item;
+        int item, parts = 1;
+        // queries to prepare here, or NULL (inner products with a counter: never)
+        const float *own = METRIC == LVQ_L2 ? a.q : nullptr;
         if (a.queue) {
             __syncthreads();
             if (tid == 0) s_item = atomicAdd(a.queue, 1);
@@ -516,10 +530,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
             item = s_item;
         } else {
             item = iter == 0 ? (int)blockIdx.x : INT32_MAX;
+            const auto *c = more_args();
+            parts = c->parts;
+            if constexpr (METRIC == LVQ_IP) own = c->q;
         }
-        if (item >= a.nq * a.parts) break;
-        const int part = a.parts > 1 ? item % a.parts : 0;
-        const int64_t list = a.order ? a.order[item] : a.parts > 1 ? item / a.parts : item;
+        if (item >= a.nq * parts) break;
+        const int part = parts > 1 ? item % parts : 0;
+        const int64_t list = a.queue ? a.order[item] : parts > 1 ? item / parts : item;
         int64_t e0 = a.offsets[list], e1 = a.offsets[list + 1];
         if (e0 < 0 || e1 < e0 || e1 > a.total) {
             if (tid == 0) atomicOr(a.err, kErrBadOffsets);
@@ -527,8 +544,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
         }
         // this item's entries: whole blocks of them per part
         int64_t skip = 0;
-        if (a.parts > 1) {
-            const int64_t run = ((e1 - e0 + a.parts - 1) / a.parts + kPairsPerBlock - 1) / kPairsPerBlock * kPairsPerBlock;
+        if (parts > 1) {
+            const int64_t run = ((e1 - e0 + parts - 1) / parts + kPairsPerBlock - 1) / kPairsPerBlock * kPairsPerBlock;
             skip = min(e1 - e0, part * run);
             e0 += skip;
             e1 = min(e1, e0 + run);
@@ -536,11 +553,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
 
         // ---- per-list query tables in LDS
         __syncthreads();
-        const float *qv = a.q ? a.q + list * a.dim : a.qk + list * a.kpos;
-        for (int sp = tid; sp < a.kpos; sp += 256) {
+        // (opaque: addresses made from them would be kept in registers for every item)
+        int st = tid;
+        asm volatile("" : "+v"(st));
+        const int sl = st & 63;
+        const int dim = METRIC == LVQ_L2 ? a.dim : own ? more_args()->dim : 0;
+        const int32_t *kdim = METRIC == LVQ_L2 ? a.kdim : own ? more_args()->kdim : nullptr;
+        const float *qv = own ? own + list * dim : a.qk + list * a.kpos;
+        for (int sp = st; sp < a.kpos; sp += 256) {
             float v;
-            if (a.q) {
-                const int j = a.kdim[sp];
+            if (own) {
+                const int j = kdim[sp];
                 v = j >= 0 ? qv[j] : 0.0f;
             } else {
                 v = qv[sp];
@@ -555,51 +578,55 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
             }
         }
         if (MASK)
-            for (int sp = tid; sp < a.kpos; sp += 256) mtab[qtab_index<B1, CH>(sp, npieces)] = a.kmask[sp];
+            for (int sp = st; sp < a.kpos; sp += 256) mtab[qtab_index<B1, CH>(sp, npieces)] = a.kmask[sp];
         if constexpr (METRIC == LVQ_IP) {
-            if (a.q) {
+            if (own) {
                 // sum(q) and c_m (of the list's means where it names them), as
                 // the preparation kernel sums them: a wave each
                 if (wave == 0) {
                     float s = 0.0f;
-                    for (int j = lane; j < a.dim; j += 64) s += qv[j];
+                    for (int j = sl; j < dim; j += 64) s += qv[j];
                     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-                    if (lane == 0) s_qsum = s;
+                    if (sl == 0) s_qsum = s;
                 }
+                const float *means = more_args()->means;
                 const int nm = a.list_means ? a.list_nmeans : a.n_means;
                 for (int t = wave; t < nm; t += 4) {
                     const int m = a.list_means ? a.list_means[list * nm + t] : t;
-                    const float *mu = a.means + (int64_t)m * a.dim;
+                    const float *mu = means + (int64_t)m * dim;
                     float s = 0.0f;
-                    for (int j = lane; j < a.dim; j += 64) s = fmaf(qv[j], mu[j], s);
+                    for (int j = sl; j < dim; j += 64) s = fmaf(qv[j], mu[j], s);
                     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-                    if (lane == 0) cmt[m] = s;
+                    if (sl == 0) cmt[m] = s;
                 }
             } else {
-                for (int m = tid; m < cm_n; m += 256) cmt[m] = a.cm[list * a.n_means + m];
-                if (tid == 0) s_qsum = a.qsum[list];
+                for (int m = st; m < cm_n; m += 256) cmt[m] = a.cm[list * a.n_means + m];
+                if (st == 0) s_qsum = a.qsum[list];
             }
         }
         if (sub)
-            for (int t = tid; t < ntab; t += 256) tmap[a.list_means[list * ntab + t]] = (uint8_t)t;
+            for (int t = st; t < ntab; t += 256) tmap[a.list_means[list * ntab + t]] = (uint8_t)t;
         if (seg)
-            for (int p = tid; p < nseg; p += 256) {
+            for (int p = st; p < nseg; p += 256) {
                 const int m = a.list_means[list * nseg + p];
                 sbase[p] = a.seg_offs[m];
                 sstart[p + 1] = a.seg_offs[m + 1] - a.seg_offs[m];   // sizes, summed below
             }
         __syncthreads();
         if (seg) {
-            if (tid == 0) {
+            if (st == 0) {
                 sstart[0] = -skip;   // (counted from the item's first entry)
                 for (int p = 0; p < nseg; ++p) sstart[p + 1] += sstart[p];
             }
             __syncthreads();
         }
-        float qsum = METRIC == LVQ_IP ? s_qsum : 0.0f;
-        // (see CandArgs::idle_slots: adds 0, or NaN)
-        if constexpr (METRIC == LVQ_IP)
-            for (int sp = 0; sp < a.idle_slots; ++sp) qsum = fmaf(qtab[qtab_index<B1, CH>(sp, npieces)], 0.0f, qsum);
+        float qsum = 0.0f;
+        if constexpr (METRIC == LVQ_IP) {
+            // (see CandArgs::idle_slots: a lane each, which adds nothing, or NaN)
+            const float v = lane < a.idle_slots ? qtab[qtab_index<B1, CH>(lane, npieces)] * 0.0f : 0.0f;
+            qsum = __ballot(v != v) ? __builtin_nanf("") : s_qsum;
+            qsum = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(qsum)));
+        }
         QRegs<B1, CH, NCH> qr;
         if constexpr (QREG) {
 #pragma unroll
@@ -729,15 +756,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
             if (lane == 0) s_got[wave] = nw;
             __syncthreads();
             if (wave == 0) {
+                int ml = lane;   // (opaque, as above)
+                asm volatile("" : "+v"(ml));
                 int n = 0;
                 for (int w = 0; w < 4; ++w) {
                     const int gw = s_got[w];
-                    for (int i = lane; i < gw; i += 64) merge[n + i] = keys[(size_t)w * a.cw + i];
+                    for (int i = ml; i < gw; i += 64) merge[n + i] = keys[(size_t)w * a.cw + i];
                     n += gw;
                 }
                 const int got = wave_compact_lean(merge, n, k, keys);
-                uint64_t *dst = a.parts > 1 ? a.part_keys + (list * a.parts + part) * k : nullptr;
-                for (int i = lane; i < k; i += 64) {
+                uint64_t *dst = parts > 1 ? more_args()->part_keys + (list * parts + part) * k : nullptr;
+                for (int i = ml; i < k; i += 64) {
                     if (dst) {
                         dst[i] = i < got ? merge[i] : kNoKey;
                         continue;

@@ -67,7 +67,10 @@ constexpr CandKernel cand_kernel_for(int variant)
 {
     constexpr CandShape sh = kCandShapes[S];
     constexpr int depth = (sh.pipe & 1) ? ((sh.pipe & 4) ? 2 : 1) : 0;
-    constexpr int W = (sh.pipe & 8) ? 6 : 2;   // (a few registers over half the file would halve the waves)
+    // (a few registers over half the file would halve the waves.  At six waves
+    // the kept orders spill little at the first level, but a lot at both:
+    // 3,000 lists of 1,000 at 4x8 d = 96, L2: 328 us, as they come 159 us)
+    constexpr int W = (sh.pipe & 8) && !((sh.pipe & 16) && B2 != 0) ? 6 : 2;
     constexpr int O = (sh.pipe & 16) ? kOrdQuads : (sh.pipe & 32) ? kOrdHalves : kOrdLane;
     constexpr bool masked_only = sh.g == 4 && sh.ch == 16 && O == kOrdQuads;
     if constexpr (!masked_only) {

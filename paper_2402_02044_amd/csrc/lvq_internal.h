@@ -79,7 +79,8 @@ struct CandArgs {
     int row_bytes, resid_bytes;
     int kchunks, kpos;
     int64_t capacity;
-    const float *q;          // nq x dim queries the kernel prepares itself, or NULL: qk, qsum, cm
+    const float *q;          // nq x dim queries the kernel prepares itself, or NULL (as for an inner
+                             //   product with a queue): qk, qsum, cm
     const int32_t *kdim;     //   hold them (kernel order, sum(q), c_m); kdim: dimension per slot
     const float *means;      //   M x dim
     int dim;
