@@ -339,6 +339,10 @@ bool shape_fits(const Format &f, void *(*lookup)(int, int, int), int bits2, int 
     return !t.pipe || t.g * t.ch * t.nch >= f.kchunks * 16;
 }
 
+// Short rows: up to this many workgroups per compute unit run as they come,
+// without an order and a counter, resident or not (see host_distances).
+constexpr int kShortRowsPerUnit = 6;
+
 // Default tile shape: the layout measured fastest among those that give every
 // value with the order of sums of order_shape, so that results do not depend
 // on the choice.  Microseconds for 3.0e6 pairs of 3,000 ragged lists, top-10
@@ -359,9 +363,19 @@ bool shape_fits(const Format &f, void *(*lookup)(int, int, int), int bits2, int 
 //                      d = 512 IP 551 / 317, L2 529 / 320
 //   padding positions  33 up to 128 B (8-bit d = 100 L2 586 / 137), 10 up to 512
 //                      B (8-bit d = 333 L2 636 / 303)
+// Many lists per compute unit (per_unit) of few entries each (avg) keep the
+// 16-lane shape where it was faster for them, microseconds (16-lane / above):
+// below 32 entries the first level in up to 128 B (3,000 lists of 20, IP, 8-bit d
+// = 96 65 / 73, d = 128 66 / 75, of 50 76 / 74 and 78 / 78; both levels gain: 4x8
+// d = 96 73 / 67); with both levels of 4-bit codes the 8-lane shapes hold two
+// waves per SIMD, the 16-lane one four, which hide the lists' set-up (4x8 d = 768 IP, 10,000 lists of 50 269 / 276, of
+// 100 366 / 350, 3,000 of 50 108 / 99; d = 192 10,000 of 100 308 / 316; L2 d = 768
+// 3,000 of 50 89 / 93, of 400 258 / 267, of 1,000 581 / 560; 16 means, of 5 131 /
+// 148, of 20 158 / 159).
 // *idle: query slots a lane without a piece multiplied by zero codes in the
 // 16-lane shape (see CandArgs::idle_slots).
-int default_shape(const Format &f, void *(*lookup)(int, int, int), int bits2, int variant, int *idle)
+int default_shape(const Format &f, void *(*lookup)(int, int, int), int bits2, int variant, double per_unit,
+                  double avg, int *idle)
 {
     const int base = order_shape(f, lookup, bits2, variant);
     *idle = 0;
@@ -376,6 +390,10 @@ int default_shape(const Format &f, void *(*lookup)(int, int, int), int bits2, in
         else if (bytes <= 96 && !(b4 && both)) pick = 31;
         else if (bytes <= 128 && !both && !(b4 && variant == 1)) pick = 32;
         else pick = one && (ip ? b4 == both : !b4 && !both) ? 35 : 34;
+        const bool deep = pick >= 34 && b4 && both;
+        const double few = deep ? (ip ? 100.0 : one ? 512.0 : 20.0) : pick > 32 || both ? 0.0 : 32.0;
+        const double from = !deep ? kShortRowsPerUnit : !ip && bytes > 192 && avg >= 32.0 ? 10.0 : 16.0;
+        if (per_unit > from && avg < few) return base;
     } else if (t.g == 16 && t.ch == 16 && t.nch == 2) {
         if (variant >= 3) pick = bytes <= 128 ? 33 : 10;
         else pick = one ? 18 : 10;
@@ -784,9 +802,12 @@ int lvq::host_distances(lvq_index *ix, const float *q_dev, int64_t nq, const int
     auto lookup = f.bits1 == 4 ? cand_kernel_b4 : cand_kernel_b8;
     int shape = force_shape >= 0 ? force_shape : ix->cand_shape[level == LVQ_FULL][k > 0];
     int idle_slots = 0;
+    // entries per list (one whose entries are not counted on the host is taken
+    // as its means' share of the store)
+    const double avg = total == INT64_MAX ? (double)ix->list_len * list_nmeans / ix->n_means : (double)total / nq;
     if (!shape_fits(f, lookup, bits2, variant, shape)) {
         if (force_shape >= 0) return LVQ_ERR_UNSUPPORTED;
-        shape = default_shape(f, lookup, bits2, variant, &idle_slots);
+        shape = default_shape(f, lookup, bits2, variant, (double)nq / ix->n_cu, avg, &idle_slots);
     }
     void *kern = shape >= 0 ? lookup(bits2, variant, shape) : nullptr;
     if (!kern) return LVQ_ERR_UNSUPPORTED;
@@ -829,10 +850,10 @@ int lvq::host_distances(lvq_index *ix, const float *q_dev, int64_t nq, const int
     // A batch that leaves workgroups idle has its lists split: parts of at
     // least one block of candidates, and more where a part builds many query
     // tables.  One list of 256 at 4x8 d = 768: 31 us whole, 20 us in
-    // eight parts, merge included; 5,000 entries 323 and 26 us.  (A list whose entries are not counted on
-    // the host is taken as its means' share of the store.)
+    // eight parts, merge included; 5,000 entries 323 and 26 us.
     const int ppb = 4 * (64 / tile_shape(shape).g);
-    const double avg = total == INT64_MAX ? (double)ix->list_len * list_nmeans / ix->n_means : (double)total / nq;
+    const TileShape ts = tile_shape(shape);
+    const bool quads = (ts.pipe & 16) && ts.ch == 8;   // the four-lane shapes of short rows
     int parts = (int)std::min<double>((double)(slots / nq), avg / (ppb * (1.0 + ntab * f.kpos / 4096)));
     // The query buffers are sized whatever this call's route is, so that a later
     // captured call of as many queries finds room (one that does not need them
@@ -859,8 +880,12 @@ int lvq::host_distances(lvq_index *ix, const float *q_dev, int64_t nq, const int
         parts = (int)std::min<size_t>(parts, room > keys_at ? (room - keys_at) / per_part : 0);
     }
     parts = std::max(1, parts);
-    // every item resident at once: no order, no counter
-    const bool queued = nq * parts > slots;
+    // Every item resident at once: no order, no counter; nor with the four-lane
+    // shapes of short rows up to 1.5 times as many, where the two launches cost
+    // more than the order gives (1,500 lists at 4x8 d = 96, both levels, L2, ordered
+    // / as they come: of 20 entries 39 / 17 us, of 400 61 / 43, of 30 to 2,000 61 /
+    // 66; with longer rows 4x8 d = 768 L2, of 30 to 2,000 163 / 231).
+    const bool queued = nq * parts > (quads ? std::max(slots, (int64_t)kShortRowsPerUnit * ix->n_cu) : slots);
     if (queued && !l2 && !prep) {
         prep = true;   // (of whole lists: no keys behind the queries)
         if (ws && (rc = size_queries(ix, *ws, nq))) return rc;
@@ -924,7 +949,13 @@ int lvq::host_distances(lvq_index *ix, const float *q_dev, int64_t nq, const int
         // persistent launch: lists longest-first from a device work counter
         LVQ_HIP(launch_list_order(offsets_dev, nq, sc.order, sc.queue, s));
     }
-    const int64_t grid = std::min<int64_t>(nq * parts, slots);
+    // (less than two lists per workgroup: equal rounds of them, with at least three
+    // workgroups per unit to hide each other's waits: 1,500 lists of 20 at 8-bit d =
+    // 512 IP, room for 1,024: 49 us, 768 workgroups 46; 1,100 of 30 to 2,000 117
+    // and 114)
+    const int64_t grid = !queued         ? nq * parts
+                         : nq < 2 * slots ? std::min(slots, std::max((nq + 1) / 2, 3 * (int64_t)ix->n_cu))
+                                          : slots;
     ix->last_wg = grid;
     ix->last_lists = nq;
     ix->last_parts = 0;

@@ -843,3 +843,32 @@ def test_vector_scan_in_a_fixed_workspace(L):
             np.testing.assert_array_equal(got[1].cpu().numpy().astype(np.float64), want[1][:5])
     assert ix.sync() == 0
     ix.close()
+
+
+@pytest.mark.parametrize("d,b1,b2,ip,M,lens", [
+    (96, 8, 0, 1, 1, (31, 33)), (128, 8, 0, 0, 1, (31, 33)), (64, 4, 0, 1, 3, (31, 33)),       # first level, 32 entries
+    (768, 4, 8, 1, 1, (99, 101)), (768, 4, 8, 0, 1, (500, 520)), (192, 4, 8, 0, 3, (19, 21)),  # both levels of 4 bits
+    (96, 4, 8, 0, 1, (20, 40))])
+def test_tile_shape_by_list_length(L, d, b1, b2, ip, M, lens):
+    """The default tile shape depends on how many lists there are per compute
+    unit and how long they are, and so does whether they run in order; values
+    and top-k do not: batches on both sides of every line give, list by list,
+    the bits of the 16-lane shape."""
+    g = synth.rng(9000 + d, b1 + b2 + ip)
+    n, k, level = 700, 10, L.LVQ_FULL if b2 else L.LVQ_PRIMARY
+    X = g.standard_normal((n, d)).astype(np.float32)
+    ix = L.Index(d, b1, b2, L.LVQ_IP if ip else L.LVQ_L2, L.LVQ_SEQUENTIAL, capacity=n, means=X[:M] * 0.4)
+    ix.insert(torch.from_numpy(X).cuda())
+    for nq in (1300, 1537, 2561, 4097):
+        Q = torch.from_numpy(g.standard_normal((nq, d)).astype(np.float32)).cuda()
+        for m in lens:
+            offs = torch.arange(nq + 1, device="cuda") * m
+            ids = torch.from_numpy(g.integers(0, n, nq * m).astype(np.int32)).cuda()
+            got = ix.distances(Q, offs, ids, level=level, k=k)
+            ix.set_tile(level, True, 1)
+            want = ix.distances(Q, offs, ids, level=level, k=k)
+            ix.set_tile(level, True, -1)
+            for a, b in zip(got, want):
+                assert torch.equal(a, b)
+    assert ix.sync() == 0
+    ix.close()
