@@ -1068,6 +1068,7 @@ static int topk_mfma(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq,
                      int32_t *ids_dev, float *dist_dev, hipStream_t s, uint32_t epoch);
 
 constexpr int64_t kPairsMaxQueries = 8;
+constexpr int kScanFewQueries = 4;   // of the small tiles
 
 // The FP32 vector scan of a format: the kernel that processes a whole row in
 // one round with the least padding, and whether it takes nq queries at this k.
@@ -1152,37 +1153,43 @@ static bool scan_plan(const lvq_index *ix, int64_t nq, int32_t k, int32_t level,
 // Row parts of the FP32 vector scan: the count with the least modelled time, in
 // rows of one workgroup.  A compute unit runs its c = workgroups / units at
 // once up to the resident ones; they share its vector ALUs, so the time is c
-// times one's rows, more where too few are resident to hide each other's
-// loads (600 queries over 300,000 rows of d = 96: one per unit 1,908 us, two
-// 1,136, three 970).  A part costs about three rounds of rows more (its first
-// rounds append nearly every row), and at the end k keys in the merge, whose
-// time does not grow with the row: about k / 4 rows of d = 96 (a tenth of the
-// keys where lists are folded whole, k > 64).  One query, top-10: d = 96,
-// 300,000 rows 55 us with 256 parts, 67 with 512, 117 with 1,024; 4x8 d = 768 204,
-// 182 and 223 us.  Parts of at least one round, and at most 20,480 keys to
-// merge per query.
+// times one's rounds of 256 rows, more where too few are resident to hide each
+// other's loads (600 queries over 300,000 rows of d = 96: one per unit 1,908 us, two
+// 1,136, three 970).  A part costs a round to begin with, its first three rounds
+// twice the others (they append nearly every row), and every part the more the more queries its tile
+// has: their keys, sorted without the other parts' bounds, and k of each to
+// merge, whose time does not grow with the row (a tenth of the keys where lists
+// are folded whole, k > 64).  Top-10, L2, 500,000 rows of d = 96: one query 68 us
+// with 256 parts, 77 with 512, 97 with 128; sixteen 221, 301, 253; top-100 sixteen
+// 405 us with 128, 441 with 203; 50,000 rows, sixteen: 88 us in parts of one round,
+// 128 of 266 rows, 114 of 1,042.  4x8 d = 768, eight queries over 500,000: 558 us
+// with 256, 386 with 512, 418 with 1,024.  At most 20,480 keys to merge per query.
 //
 // Under a memory budget no more than four workgroups of sixteen queries per
 // unit and 1,024 rows per part: the keys are charged to the budget, and the
 // counts above can ask for 16 times as many (nq x parts x k keys).
 static int64_t scan_parts_fp32(const lvq_index *ix, const ScanPlan &pl, int64_t nq, int32_t k, int64_t n_rows)
 {
-    const double merge = (k <= 64 ? 0.25 : 0.1) * k * 96.0 / ix->f.kpos;
+    const double queries = (double)std::min<int64_t>(nq, pl.tq);
+    const double merge = (k <= 64 ? 0.25 : 0.1) * k * 96.0 / ix->f.kpos *
+                         (1.2 + (k <= 64 ? 0.25 : 0.1) * queries);
     const int64_t qtiles = (nq + pl.tq - 1) / pl.tq, occ = std::max<int64_t>(1, pl.slots / ix->n_cu);
-    int64_t most = std::max<int64_t>(1, std::min<int64_t>({n_rows / 256, (int64_t)(ix->lds_max / 8 - k) / k,
+    int64_t most = std::max<int64_t>(1, std::min<int64_t>({(n_rows + 255) / 256, (int64_t)(ix->lds_max / 8 - k) / k,
                                                            2 * pl.slots / qtiles + 1}));
     if (ix->cfg.mem_budget_bytes > 0) {
         const int64_t tiles16 = (nq + 15) / 16;
         most = std::min(most, std::max<int64_t>(1, std::min<int64_t>((4 * (int64_t)ix->n_cu + tiles16 - 1) / tiles16,
                                                                      n_rows / 1024)));
     }
-    auto shared = [](int64_t c) { return (double)c * (c == 1 ? 1.77 : c == 2 ? 1.14 : 1.0); };
+    const double two = pl.tq == kScanFewQueries ? 1.22 : 1.14;
+    auto shared = [two](int64_t c) { return (double)c * (c == 1 ? 1.77 : c == 2 ? two : 1.0); };
     int64_t parts = 1;
     double best = 0.0;
     for (int64_t p = 1; p <= most; ++p) {
         const int64_t c = (qtiles * p + ix->n_cu - 1) / ix->n_cu;
-        const double cost = ((double)(c / occ) * shared(occ) + shared(c % occ)) *
-                            ((double)((n_rows + p - 1) / p) + 768.0) + merge * (double)p;
+        const double rounds = (double)(((n_rows + p - 1) / p + 255) / 256), first = std::min(rounds, 3.0);
+        const double cost = ((double)(c / occ) * shared(occ) + shared(c % occ)) * 256.0 * (rounds + first + 1.0) +
+                            merge * (double)p * first / 3.0;
         if (p == 1 || cost < best) {
             best = cost;
             parts = p;
@@ -1339,13 +1346,18 @@ int lvq::host_topk(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq, i
     if (rc) return rc;
     Workspace &w = workspace(ix, s);
     // Where the workspace has no room and cannot grow (a capture, a budget): the
-    // smallest tiles, or for few inner products the matrix cores; and the row
-    // parts whose keys there is room for.
-    if ((rc = dev_alloc(ix, w.qk, scan_table_bytes(ix, nq, pl.tq)))) {
+    // bounds behind the table, the smallest tiles, or for few inner products the
+    // matrix cores; and the row parts whose keys there is room for.
+    const bool own_bounds = dev_alloc(ix, w.gthr, sizeof(uint32_t) * (size_t)nq) == LVQ_OK;
+    if (!own_bounds) (void)hipGetLastError();
+    auto table = [&]() {
+        return dev_alloc(ix, w.qk, scan_table_bytes(ix, nq, pl.tq) - (own_bounds ? sizeof(uint32_t) * (size_t)nq : 0));
+    };
+    if ((rc = table())) {
         (void)hipGetLastError();
         if (pl.pair_chunk) return topk_mfma(ix, q_dev, LVQ_FP32, nq, k, level, ids_dev, dist_dev, s, epoch);
         if (!scan_plan(ix, nq, k, level, &pl, true)) return rc;
-        if ((rc = dev_alloc(ix, w.qk, scan_table_bytes(ix, nq, pl.tq)))) return rc;
+        if ((rc = table())) return rc;
     }
     const int tq = pl.tq;
     const int64_t qtiles = (nq + tq - 1) / tq;
@@ -1363,7 +1375,8 @@ int lvq::host_topk(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq, i
         parts = std::max<int64_t>(1, std::max<int64_t>(parts / 2, std::min<int64_t>(parts - 1, w.part.bytes / per_part)));
     }
     const int64_t rows_per_part = std::max<int64_t>(1, (n_rows + parts - 1) / parts);
-    uint32_t *bounds = reinterpret_cast<uint32_t *>(P<float>(w.qk) + qtiles * tq * f.kpos);
+    uint32_t *bounds = own_bounds ? P<uint32_t>(w.gthr)
+                                  : reinterpret_cast<uint32_t *>(P<float>(w.qk) + qtiles * tq * f.kpos);
     LVQ_HIP(launch_prep_rows(prep_args(ix, (const float *)q_dev, nq, P<float>(w.qk), P<float>(w.qsum), P<float>(w.cm)),
                              P<float>(ix->muk), tq, pl.pair_chunk, bounds, s));
 
