@@ -1155,8 +1155,8 @@ static bool scan_plan(const lvq_index *ix, int64_t nq, int32_t k, int32_t level,
 // once up to the resident ones; they share its vector ALUs, so the time is c
 // times one's rounds of 256 rows, more where too few are resident to hide each
 // other's loads (600 queries over 300,000 rows of d = 96: one per unit 1,908 us, two
-// 1,136, three 970).  A part costs a round to begin with, its first three rounds
-// twice the others (they append nearly every row), and every part the more the more queries its tile
+// 1,136, three 970).  A part costs a round of d = 96 to begin with, its first
+// three rounds another each (they append nearly every row), and every part the more the more queries its tile
 // has: their keys, sorted without the other parts' bounds, and k of each to
 // merge, whose time does not grow with the row (a tenth of the keys where lists
 // are folded whole, k > 64).  Top-10, L2, 500,000 rows of d = 96: one query 68 us
@@ -1181,16 +1181,21 @@ static int64_t scan_parts_fp32(const lvq_index *ix, const ScanPlan &pl, int64_t 
         most = std::min(most, std::max<int64_t>(1, std::min<int64_t>((4 * (int64_t)ix->n_cu + tiles16 - 1) / tiles16,
                                                                      n_rows / 1024)));
     }
-    const double two = pl.tq == kScanFewQueries ? 1.22 : 1.14;
+    const double begin = std::min(1.0, 96.0 / ix->f.kpos);
+    const double two = pl.tq == kScanFewQueries && ix->f.kchunks <= 6 ? 1.22 : 1.14;
     auto shared = [two](int64_t c) { return (double)c * (c == 1 ? 1.77 : c == 2 ? two : 1.0); };
     int64_t parts = 1;
     double best = 0.0;
-    for (int64_t p = 1; p <= most; ++p) {
+    // (the fewest parts of every number of rounds: more cost more)
+    for (int64_t p = most, next; p >= 1; p = next) {
+        const int64_t n = ((n_rows + p - 1) / p + 255) / 256;
+        if (n > 0) p = std::min(p, (n_rows + 256 * n - 1) / (256 * n));
+        next = p - 1;
         const int64_t c = (qtiles * p + ix->n_cu - 1) / ix->n_cu;
-        const double rounds = (double)(((n_rows + p - 1) / p + 255) / 256), first = std::min(rounds, 3.0);
-        const double cost = ((double)(c / occ) * shared(occ) + shared(c % occ)) * 256.0 * (rounds + first + 1.0) +
+        const double rounds = (double)n, first = std::min(rounds, 3.0);
+        const double cost = ((double)(c / occ) * shared(occ) + shared(c % occ)) * 256.0 * (rounds + first + begin) +
                             merge * (double)p * first / 3.0;
-        if (p == 1 || cost < best) {
+        if (p == most || best == 0.0 || cost <= best) {
             best = cost;
             parts = p;
         }
@@ -1294,22 +1299,27 @@ static int64_t scan_parts_wide(const lvq_index *ix, int64_t qtiles, int32_t k, i
     const int64_t max_parts = std::max<int64_t>(
         1, std::min<int64_t>(n_rows / (sm.parts ? 512 : 4096), (int64_t)(ix->lds_max / 8 - k) / k));
     const double sampled = (double)std::max<int64_t>(1, sm.parts * sm.rows);
+    const double warm = 1024.0 * k, row_cost = prec == LVQ_FP32 ? 8.0 : 1.0;
+    const double least = (sm.parts ? 2200.0 : 10240.0) / row_cost;   // of any tile
+    auto later = [&](int64_t iters) { return sm.parts ? 1.0 + 0.025 / row_cost * (double)(iters - 1) : 1.0; };
     int64_t parts = 1;
     double best = 0.0;
-    for (int64_t p = 1; p <= max_parts; ++p) {
-        const int64_t tiles = qtiles * p;
-        const int64_t g = std::min<int64_t>(slots, (tiles + 7) / 8 * 8);
-        const int64_t per_xcd = (tiles + 7) / 8;
-        const int64_t iters = (per_xcd + g / 8 - 1) / (g / 8);
-        const double rows = (double)((n_rows + p - 1) / p), warm = 1024.0 * k;
-        const double row_cost = prec == LVQ_FP32 ? 8.0 : 1.0;
+    // (the most parts of every number of tiles per workgroup: with more, shorter
+    // tiles the time falls as long as that number stays)
+    for (int64_t i = (qtiles + slots - 1) / slots;; ++i) {
+        const int64_t most = std::min(max_parts, i * slots / qtiles);
+        const int64_t n = (n_rows + most - 1) / most;                      // rows per part,
+        const int64_t p = n > 0 ? (n_rows + n - 1) / n : 1;                // and the fewest such parts
+        const int64_t iters = (qtiles * p + slots - 1) / slots;
+        const double rows = (double)n;
         const double extra = sm.parts ? 2200.0 + 16.0 * k * (rows < sampled ? rows / sampled : 1.0 + std::log(rows / sampled))
                                       : 10240.0 + 0.5 * warm * (1.0 + std::log(std::max(1.0, rows / warm)));
-        const double cost = (double)iters * (rows + extra / row_cost) * (sm.parts ? 1.0 + 0.025 / row_cost * (double)(iters - 1) : 1.0);
-        if (p == 1 || cost < best) {
+        const double cost = (double)iters * (rows + extra / row_cost) * later(iters);
+        if (best == 0.0 || cost < best) {
             best = cost;
             parts = p;
         }
+        if (most == max_parts || (double)(i + 1) * least * later(i + 1) >= best) break;
     }
     *grid = std::min<int64_t>(slots, (qtiles * parts + 7) / 8 * 8);
     return parts;
@@ -1471,7 +1481,12 @@ static int topk_mfma(lvq_index *ix, const void *q_dev, int32_t prec, int64_t nq,
     // Under a memory budget the scan is sized as without a sample, and where the
     // buffers have no room (a captured call), in fewer parts and without one.
     ScanSample sm = {0, 0};
-    if (qbw && ix->cfg.mem_budget_bytes <= 0) sm = scan_sample(ix, qtiles, k, n_rows, bits2, prec);
+    // One query over rows enough to fill the chip with parts of 4,096 goes without:
+    // what passes its loose bounds costs less than the pass (sample / none, d = 96
+    // top-10: 800,000 rows 97 / 86 us, 4x10^6 256 / 237; d = 768 both levels 2x10^6
+    // 682 / 672; but 300,000 76 / 80, two queries over 10^6 103 / 106, top-200 187 / 242).
+    const bool alone = nq == 1 && k <= 64 && prec != LVQ_FP32 && n_rows >= (int64_t)ix->n_cu * 3 / 4 * 4096;
+    if (qbw && !alone && ix->cfg.mem_budget_bytes <= 0) sm = scan_sample(ix, qtiles, k, n_rows, bits2, prec);
     int64_t grid = 0;
     int64_t parts = qbw ? scan_parts_wide(ix, qtiles, k, n_rows, prec, sm, &grid) : scan_parts_mfma(ix, qtiles, k, n_rows);
     for (;;) {

@@ -872,3 +872,20 @@ def test_tile_shape_by_list_length(L, d, b1, b2, ip, M, lens):
                 assert torch.equal(a, b)
     assert ix.sync() == 0
     ix.close()
+
+
+@pytest.mark.parametrize("n", [256 * 3 * 1024 - 1, 256 * 3 * 1024])
+@pytest.mark.parametrize("k", [1, 100])
+def test_one_query_without_a_sample(L, n, k):
+    """One 16-bit query over a large store starts without sampled bounds; its
+    answers are those it gets beside another query, which samples."""
+    d = 96
+    g = torch.Generator(device="cuda").manual_seed(9100)
+    x = torch.randn(4096, d, generator=g, device="cuda").repeat((n + 4095) // 4096, 1)[:n]   # ties
+    ix = L.Index(d, 8, 0, L.LVQ_IP, L.LVQ_SEQUENTIAL, capacity=n)
+    ix.insert(x.contiguous())
+    q = torch.randn(2, d, generator=g, device="cuda").to(torch.bfloat16)
+    one, two = ix.topk(q[:1].contiguous(), k), ix.topk(q, k)
+    assert ix.sync() == 0
+    assert torch.equal(one[0], two[0][:1]) and torch.equal(one[1], two[1][:1])
+    ix.close()
