@@ -220,9 +220,10 @@ int lvq_tile_shape(int32_t shape, int32_t *lanes, int32_t *piece_bytes, int32_t 
 /* Exhaustive top-k over every slot live at the call (Sec. 2.1 k-NN problem),
  * for nq queries q_dev (nq x dim) of precision prec at `level`: LVQ_FP32
  * takes float queries and FP32 products -- on the FP32 matrix cores
- * (v_mfma_f32_32x32x2_f32, codes converted exactly) for the first-level inner
- * product of an index with one mean and k <= 512, else on the vector ALUs
- * (which take small batches of those too, with the same values);
+ * (v_mfma_f32_32x32x2_f32, codes converted exactly) for inner products at the
+ * first level or with 8-bit residual codes, k <= 512 and any number of means
+ * whose terms fit the LDS beside the queries, else on the vector ALUs (which
+ * take batches of up to eight of those too, with the same values);
  * LVQ_BF16 / LVQ_FP16 take queries already in that type and run matrix-core
  * (MFMA) products of queries and exactly converted integer codes with FP32
  * accumulation (inner product; both levels need 8-bit residual codes).

@@ -864,19 +864,18 @@ int lvq::host_distances(lvq_index *ix, const float *q_dev, int64_t nq, const int
     const size_t qk_bytes = sizeof(float) * (size_t)nq * f.kpos, keys_at = prep ? (qk_bytes + 255) & ~(size_t)255 : 0;
     const size_t per_part = sizeof(uint64_t) * (size_t)nq * k;
     Workspace *ws = fixed ? nullptr : &workspace(ix, s);
+    const size_t want = keys_at + (k > 0 && parts > 1 ? parts * per_part : 0);
+    if (ws && want > keys_at && ws->qk.bytes < want && !ix->capturing && !ws->qk.pinned && ix->cfg.mem_budget_bytes <= 0) {
+        size_t grow = 65536;   // (doubled, so that it seldom grows: that waits for the device)
+        while (grow < std::max(want, scan_table_bytes(ix, nq, 16))) grow *= 2;
+        if (dev_alloc(ix, ws->qk, grow) != LVQ_OK) (void)hipGetLastError();
+    }
     if (ws && (rc = size_queries(ix, *ws, nq))) {
         if (prep) return rc;
         (void)hipGetLastError();
     }
     if (k > 0 && parts > 1) {
-        size_t room = fixed ? (prep ? 0 : fixed->bytes) : ws->qk.bytes;
-        const size_t want = keys_at + parts * per_part;
-        if (!fixed && room < want && !ix->capturing && !ws->qk.pinned && ix->cfg.mem_budget_bytes <= 0) {
-            size_t grow = 65536;
-            while (grow < want) grow *= 2;
-            if (dev_alloc(ix, ws->qk, std::max(grow, qk_bytes)) != LVQ_OK) (void)hipGetLastError();
-            room = ws->qk.bytes;
-        }
+        const size_t room = fixed ? (prep ? 0 : fixed->bytes) : ws->qk.bytes;
         parts = (int)std::min<size_t>(parts, room > keys_at ? (room - keys_at) / per_part : 0);
     }
     parts = std::max(1, parts);
@@ -1130,8 +1129,10 @@ static bool scan_plan(const lvq_index *ix, int64_t nq, int32_t k, int32_t level,
         if (t.g * t.ch * t.nch < b.g * b.ch * b.nch) shape = i;
     }
     if (shape < 0) return false;
-    // the largest k taken: 16 queries of kpos values and of k + 512 / g rows'
-    // keys, c_m and 4 k keys of scratch within one workgroup's LDS
+    // The sizes taken are those of a scan that held 16 queries of kpos values, k +
+    // 512 / g keys of each, c_m and 4 k keys of scratch in one workgroup's LDS:
+    // larger ones stay refused.  (The kernel itself keeps no queries there and needs
+    // less, which is tested below.)
     const size_t need = (size_t)16 * f.kpos * 4 + (((size_t)16 * (((nm + 1) & ~1) + 2) * 4 + 15) & ~(size_t)15) + 256 +
                         ((size_t)16 * (k + 512 / tile_shape(shape).g) + 4 * (size_t)k) * 8;
     if (need > ix->lds_max) return false;
@@ -1163,7 +1164,8 @@ static bool scan_plan(const lvq_index *ix, int64_t nq, int32_t k, int32_t level,
 // with 256 parts, 77 with 512, 97 with 128; sixteen 221, 301, 253; top-100 sixteen
 // 405 us with 128, 441 with 203; 50,000 rows, sixteen: 88 us in parts of one round,
 // 128 of 266 rows, 114 of 1,042.  4x8 d = 768, eight queries over 500,000: 558 us
-// with 256, 386 with 512, 418 with 1,024.  At most 20,480 keys to merge per query.
+// with 256, 386 with 512, 418 with 1,024.  At most 20,480 keys per query, a bound on the scratch (the merge
+// takes any number).
 //
 // Under a memory budget no more than four workgroups of sixteen queries per
 // unit and 1,024 rows per part: the keys are charged to the budget, and the
@@ -1207,8 +1209,9 @@ static int64_t scan_parts_fp32(const lvq_index *ix, const ScanPlan &pl, int64_t 
 // Time model: whole rounds of workgroups over the compute units, each
 // workgroup streaming n_rows / parts rows, plus a per-part overhead (a part
 // starts with a loose top-k bound and adds k keys to the merge) of 2% of a
-// part's scan per extra part.  Parts keep at least 64 row rounds, and the
-// merge (parts * k keys, + k) fits one workgroup's LDS.
+// part's scan per extra part.  Parts keep at least 64 row rounds,
+// and a query's keys at most 20,480 (lds_max / 8): a bound on the scratch, as the
+// merge takes any number.
 static int64_t scan_parts_mfma(const lvq_index *ix, int64_t qtiles, int32_t k, int64_t n_rows)
 {
     const int64_t max_parts = std::max<int64_t>(
@@ -1291,7 +1294,7 @@ static ScanSample scan_sample(const lvq_index *ix, int64_t qtiles, int32_t k, in
 // 512 k (1 + ln(R / 1024 k)) rows' worth, and 10,240 for the rest.
 // An FP32 row costs about 8 16-bit ones (a sixteenth of the matrix-core
 // rate, half the queries per tile).  Parts keep at least 512 rows (4096 without a
-// sample), and the merge (parts * k keys, + k) fits one workgroup's LDS.
+// sample), and a query's keys at most 20,480, as above.
 static int64_t scan_parts_wide(const lvq_index *ix, int64_t qtiles, int32_t k, int64_t n_rows, int32_t prec,
                                const ScanSample &sm, int64_t *grid)
 {
