@@ -951,10 +951,11 @@ int lvq::host_distances(lvq_index *ix, const float *q_dev, int64_t nq, const int
     // (less than two lists per workgroup: equal rounds of them, with at least three
     // workgroups per unit to hide each other's waits: 1,500 lists of 20 at 8-bit d =
     // 512 IP, room for 1,024: 49 us, 768 workgroups 46; 1,100 of 30 to 2,000 117
-    // and 114)
+    // and 114; not the probe's, which make their tables between lists: 2,000 queries,
+    // two of 256 means over 10^6 rows 1,111 us with 1,000 workgroups, 1,006 with all)
     const int64_t grid = !queued         ? nq * parts
-                         : nq < 2 * slots ? std::min(slots, std::max((nq + 1) / 2, 3 * (int64_t)ix->n_cu))
-                                          : slots;
+                         : nq < 2 * slots && !segmented ? std::min(slots, std::max((nq + 1) / 2, 3 * (int64_t)ix->n_cu))
+                                                        : slots;
     ix->last_wg = grid;
     ix->last_lists = nq;
     ix->last_parts = 0;
