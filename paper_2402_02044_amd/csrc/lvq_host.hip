@@ -1157,25 +1157,27 @@ static bool scan_plan(const lvq_index *ix, int64_t nq, int32_t k, int32_t level,
 // once up to the resident ones; they share its vector ALUs, so the time is c
 // times one's rounds of 256 rows, more where too few are resident to hide each
 // other's loads (600 queries over 300,000 rows of d = 96: one per unit 1,908 us, two
-// 1,136, three 970).  A part costs a round of d = 96 to begin with, its first
-// three rounds another each (they append nearly every row), and every part the more the more queries its tile
-// has: their keys, sorted without the other parts' bounds, and k of each to
-// merge, whose time does not grow with the row (a tenth of the keys where lists
-// are folded whole, k > 64).  Top-10, L2, 500,000 rows of d = 96: one query 68 us
-// with 256 parts, 77 with 512, 97 with 128; sixteen 221, 301, 253; top-100 sixteen
-// 405 us with 128, 441 with 203; 50,000 rows, sixteen: 88 us in parts of one round,
-// 128 of 266 rows, 114 of 1,042.  4x8 d = 768, eight queries over 500,000: 558 us
-// with 256, 386 with 512, 418 with 1,024.  At most 20,480 keys per query, a bound on the scratch (the merge
-// takes any number).
+// 1,136, three 970).  A part costs 2.3 rounds of d = 96 to begin with (its
+// first ones append nearly every row), every part its k keys, sorted and merged, whose
+// time does not grow with the row (two fifths where lists are folded whole, k >
+// 64), and parts of more than one round the atomics that share the bounds, one
+// address for all parts of a query: 250,000 rows of d = 96, L2, 16 queries, top-1, 156
+// us with 128 parts, 170 with 256, 272 with 512, 392 with 768, but 197 with 977 of
+// one round; eight queries at d = 128 118, 113, 177, 217 and 101.  Top-10 of three
+// queries: 70 us with 256, 105 with 512, 84 with 977; 30,000 rows, 300 queries, 130
+// with 40, 174 with 12.  On 798 cases (10^4 to 5x10^5 rows of d = 96 to 768, 1 to
+// 700 queries, k = 1 to 100) the counts taken are 1% over the best one measured on
+// average and 8% in one of 20.  At most 20,480 keys per query, a bound on the scratch
+// (the merge takes any number).
 //
 // Under a memory budget no more than four workgroups of sixteen queries per
 // unit and 1,024 rows per part: the keys are charged to the budget, and the
 // counts above can ask for 16 times as many (nq x parts x k keys).
 static int64_t scan_parts_fp32(const lvq_index *ix, const ScanPlan &pl, int64_t nq, int32_t k, int64_t n_rows)
 {
-    const double queries = (double)std::min<int64_t>(nq, pl.tq);
-    const double merge = (k <= 64 ? 0.25 : 0.1) * k * 96.0 / ix->f.kpos *
-                         (1.2 + (k <= 64 ? 0.25 : 0.1) * queries);
+    const double keys = (k <= 64 ? 0.77 : 0.31) * k;   // to merge, per part
+    const double sorts = 0.065 * keys * std::min<int64_t>(nq, pl.tq);
+    const double bounds = 7.3 * std::min<int64_t>(nq, 20);
     const int64_t qtiles = (nq + pl.tq - 1) / pl.tq, occ = std::max<int64_t>(1, pl.slots / ix->n_cu);
     int64_t most = std::max<int64_t>(1, std::min<int64_t>({(n_rows + 255) / 256, (int64_t)(ix->lds_max / 8 - k) / k,
                                                            2 * pl.slots / qtiles + 1}));
@@ -1184,9 +1186,10 @@ static int64_t scan_parts_fp32(const lvq_index *ix, const ScanPlan &pl, int64_t 
         most = std::min(most, std::max<int64_t>(1, std::min<int64_t>((4 * (int64_t)ix->n_cu + tiles16 - 1) / tiles16,
                                                                      n_rows / 1024)));
     }
-    const double begin = std::min(1.0, 96.0 / ix->f.kpos);
-    const double two = pl.tq == kScanFewQueries && ix->f.kchunks <= 6 ? 1.22 : 1.14;
-    auto shared = [two](int64_t c) { return (double)c * (c == 1 ? 1.77 : c == 2 ? two : 1.0); };
+    const double unit = ix->f.kpos / 96.0 * (1.0 + 0.7 * pl.tq);   // a row
+    const double begin = 2.3 * std::min(1.0, 96.0 / ix->f.kpos);
+    const double two = pl.tq == kScanFewQueries && ix->f.kchunks <= 6 ? 1.38 : 1.18;
+    auto shared = [two](int64_t c) { return (double)c * (c == 1 ? 1.8 : c == 2 ? two : 1.0); };
     int64_t parts = 1;
     double best = 0.0;
     // (the fewest parts of every number of rounds: more cost more)
@@ -1195,9 +1198,9 @@ static int64_t scan_parts_fp32(const lvq_index *ix, const ScanPlan &pl, int64_t 
         if (n > 0) p = std::min(p, (n_rows + 256 * n - 1) / (256 * n));
         next = p - 1;
         const int64_t c = (qtiles * p + ix->n_cu - 1) / ix->n_cu;
-        const double rounds = (double)n, first = std::min(rounds, 3.0);
-        const double cost = ((double)(c / occ) * shared(occ) + shared(c % occ)) * 256.0 * (rounds + first + begin) +
-                            merge * (double)p * first / 3.0;
+        const double first = (double)std::min<int64_t>(n, 3) / 3.0;
+        const double cost = unit * ((double)(c / occ) * shared(occ) + shared(c % occ)) * 256.0 * ((double)n + begin) +
+                            (double)p * (keys + sorts * first + (n > 1 ? bounds : 0.0));
         if (p == most || best == 0.0 || cost <= best) {
             best = cost;
             parts = p;
